@@ -40,15 +40,14 @@ def compile_flags():
 # results are read by VALU code (softmax, epilogues, LayerNorm, the survivor
 # filter): results kept in VGPRs save one accumulator move per element (and keep
 # the filter's 128 accumulators from being copied out of AGPRs all at once).  The
-# d_model-64 encoder runs one wave per SIMD through chains of short dependent
-# steps: the iterative ILP scheduler's order of them is 7 % faster at the paper's
-# shape than the default one (the other sources gain nothing from it).  The int8
-# score kernels' division and square root must round correctly (the compiler's
-# default for HIP, stated explicitly).
+# d_model-64 encoder is made of short dependent steps: the max-ILP scheduler orders
+# them 1 - 4 % better than the default one (192 positions and fewer; the other
+# sources gain nothing from it).  The int8 score kernels' division and square root
+# must round correctly (the compiler's default for HIP, stated explicitly).
 EXTRA_FLAGS = {"encoder_fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_fused_unmasked.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm",
-                                     "-amdgpu-sched-strategy=iterative-ilp"],
+                                     "-amdgpu-sched-strategy=max-ilp"],
                "select.hip": ["-fhip-fp32-correctly-rounded-divide-sqrt"],
                "select_fused.hip": ["-fhip-fp32-correctly-rounded-divide-sqrt", "-mllvm",
                                     "-amdgpu-mfma-vgpr-form"]}

@@ -150,3 +150,41 @@ def test_repeated_runs_bitwise_identical():
     first = T.encode(tok, cand, dw).clone()
     for _ in range(2):
         assert torch.equal(T.encode(tok, cand, dw), first)
+
+
+@pytest.mark.parametrize("T_,total,kw", [
+    (1, 9, {}), (15, 600, {}), (16, 300, dict(n_heads=2)), (17, 520, {}), (33, 300, {}),
+    (128, 270, {}), (129, 30, {}), (191, 30, dict(n_heads=2)), (193, 30, {}), (257, 20, {}),
+    (385, 12, dict(d=64)), (577, 8, dict(n_layers=1, d_ffn=160)),
+    (200, 20, dict(n_layers=1, d=256)), (100, 20, dict(n_layers=1, d_ffn=96, d=128))])
+def test_tile_and_block_edges(T_, total, kw):
+    """Waves of 16 tokens, pairs of 32 keys, one block of up to 192 positions or several
+    of about one size, several short candidates to a workgroup (more than one per CU),
+    and weights that leave no room for W_in and W_pool on chip; packed weights too."""
+    print(f"encode_small edges T={T_} total={total} {kw}", flush=True)
+    rng = np.random.default_rng(T_)
+    edges = [e for e in (0, 1, 15, 16, 17, 31, 32, 33, T_ - 1, T_) if 0 <= e <= T_]
+    vl = rng.integers(0, T_ + 1, size=total)
+    vl[:min(total, len(edges))] = edges[:total]
+    tb = synth.make_tokens(total, T_, kw.get("d", 32), seed=T_, valid_len=vl.astype(np.int32))
+    ids = np.unique(np.r_[np.arange(min(total, 24)), np.arange(0, total, 17), total - 1])
+    W = weights_for(T_, **kw)
+    out = run_and_check(tb, W, ids=ids)
+    tok, cand = upload_tokens(tb)
+    assert torch.equal(T.encode(tok, cand, T.DeviceWeights(W, pack=True)), out)
+
+
+def test_tables_aligned_to_8_bytes_only():
+    """The side tables need 8-byte alignment only."""
+    tb = synth.make_tokens(40, 100, 32, seed=3)
+    tok, cand = upload_tokens(tb)
+    dw = T.DeviceWeights(weights_for(100), pack=True)
+    ref = T.encode(tok, cand, dw).clone()
+    kept = []
+    for name in ("E_act", "E_time"):
+        src = next(t for t in dw.keep if t.data_ptr() == getattr(dw.s, name))
+        buf = torch.empty(src.numel() + 4, dtype=src.dtype, device=src.device)
+        buf[4:].copy_(src.reshape(-1))
+        kept.append(buf)
+        setattr(dw.s, name, buf.data_ptr() + 8)
+    assert torch.equal(T.encode(tok, cand, dw), ref)
