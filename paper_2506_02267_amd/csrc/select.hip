@@ -8,7 +8,8 @@
 // that request straight from the one stored copy (no per-candidate broadcast).
 //
 // Top-k, one workgroup per candidate, scores as order-preserving 32-bit keys.
-// Rows of up to 4096 keys: the row is held in registers, the k-th largest key
+// Rows of up to 4096 keys: the row is held in registers and its k best keys are
+// placed by bins (place_by_bins); where many keys are equal, the k-th largest key is
 // found by a 32-step bitwise search (each step one block-wide count), every key
 // above it kept plus the lowest-indexed rows equal to it (an ordered compaction
 // by block-wide prefix sum).  Longer rows are streamed once against a threshold
@@ -34,6 +35,11 @@ namespace tav2 {
 constexpr int SC_CANDS = 128;
 constexpr int SC_ROWS = 256;
 constexpr int SC_PAD = 8;   // LDS row padding (bf16) of the candidate tile
+// Tiles x d below this: the direct kernel (d 32: 17.6 us a search against 21.5 at 64
+// tiles, 22.8 against 24.2 at 128; d 256: 18.3 against 21.4 at 12 tiles; above it, re-reading
+// the operands costs more than it saves: 45.8 against 41.3 at 128 tiles of d 256,
+// 50.5 against 34.7 at 512 of d 64).
+constexpr int64_t SC_DIRECT = 8192;
 
 __global__ __launch_bounds__(256) void score_bf16_kernel(
     const bf16_t* __restrict__ emb, const int64_t* __restrict__ seq_off,
@@ -103,6 +109,69 @@ __global__ __launch_bounds__(256) void score_bf16_kernel(
         const int64_t n = n0 + a * 32 + 8 * (reg / 4) + 4 * h + (reg % 4);
         if (n < c_end) scores[n * ld + i] = acc[a][b][reg];
       }
+    }
+  }
+}
+
+// The same scores where the 128 x 256 tiles are too few to fill the GPU: wave w of a
+// workgroup takes 32 candidates x rows 64 w .. +63, its operands straight from memory
+// with up to 16 k-blocks in flight (a wave is the only reader of its rows, and the
+// staging of a candidate tile, its barrier and a k loop one load deep were 14 us of
+// latency at 24 candidates x 3001 rows).  Same products in the same k order: the same
+// bits.
+constexpr int SD_CANDS = 32;
+constexpr int SD_D = 16;   // k-blocks in flight (all of them at d <= 256)
+__global__ __launch_bounds__(256) void score_bf16_direct_kernel(
+    const bf16_t* __restrict__ emb, const int64_t* __restrict__ seq_off,
+    const int32_t* __restrict__ seq_len, const bf16_t* __restrict__ cand,
+    const int64_t* __restrict__ cand_off, int d, int max_len, float* __restrict__ scores,
+    int64_t ld) {
+  const int r = blockIdx.z;
+  const int64_t c_end = cand_off[r + 1];
+  const int64_t n0 = cand_off[r] + int64_t(blockIdx.y) * SD_CANDS;
+  if (n0 >= c_end) return;
+  const int L = min(seq_len[r], max_len);
+  const int row0 = blockIdx.x * SC_ROWS + (threadIdx.x / WAVE) * 64;
+  if (row0 >= L) return;   // wave-uniform
+  const int lane = threadIdx.x % WAVE, h = lane / 32, l32 = lane % 32;
+  const bf16_t* seq = emb + seq_off[r] * int64_t(d);
+  const bf16_t* b0 = seq + int64_t(min(row0 + l32, L - 1)) * d + 8 * h;        // clamped; not stored
+  const bf16_t* b1 = seq + int64_t(min(row0 + 32 + l32, L - 1)) * d + 8 * h;
+  const bf16_t* arow = cand + (n0 + l32 < c_end ? n0 + l32 : c_end - 1) * d + 8 * h;
+  const int nkb = d / 16;
+  bf16x8 qa[SD_D], q0[SD_D], q1[SD_D];
+#pragma unroll
+  for (int u = 0; u < SD_D; ++u)
+    if (u < nkb) {
+      qa[u] = as_bf16x8(*reinterpret_cast<const uint4*>(arow + 16 * u));
+      q0[u] = as_bf16x8(*reinterpret_cast<const uint4*>(b0 + 16 * u));
+      q1[u] = as_bf16x8(*reinterpret_cast<const uint4*>(b1 + 16 * u));
+    }
+  f32x16 acc[2] = {f32x16{}, f32x16{}};
+  for (int kb0 = 0; kb0 < nkb; kb0 += SD_D) {
+#pragma unroll
+    for (int u = 0; u < SD_D; ++u) {
+      const int kb = kb0 + u;
+      if (kb < nkb) {   // wave-uniform
+        acc[0] = mfma32(qa[u], q0[u], acc[0]);
+        acc[1] = mfma32(qa[u], q1[u], acc[1]);
+        const int kn = kb + SD_D;
+        if (kn < nkb) {
+          qa[u] = as_bf16x8(*reinterpret_cast<const uint4*>(arow + 16 * kn));
+          q0[u] = as_bf16x8(*reinterpret_cast<const uint4*>(b0 + 16 * kn));
+          q1[u] = as_bf16x8(*reinterpret_cast<const uint4*>(b1 + 16 * kn));
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int i = row0 + b * 32 + l32;
+    if (i >= L) continue;
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg) {
+      const int64_t n = n0 + 8 * (reg / 4) + 4 * h + (reg % 4);
+      if (n < c_end) scores[n * ld + i] = acc[b][reg];
     }
   }
 }
@@ -229,12 +298,16 @@ __global__ __launch_bounds__(256) void score_f32_kernel(
 }
 
 // ---------------------------------------------------------------- top-k
-constexpr int TK_THREADS = 512;
+// NT: threads of a workgroup, PT: keys per thread (4 consecutive rows at a time).
 
 // Exclusive prefix (in thread order) and block total of NV 64-bit values per
 // thread; sw holds NV per wave.  sw is read after the one barrier inside: the
 // caller synchronizes again before sw is written by a later scan.
-template <int NV>
+// At most this many candidates (two per CU): 512 threads each, half as many keys per
+// thread (100 candidates of 2000 rows, k 256: 13.5 us a search against 17.3; more
+// candidates hide the latency themselves: 2800 of 4000 rows 33.8 against 39.7).
+constexpr int TK_WIDE = 512;
+template <int NV, int NT>
 __device__ __forceinline__ void block_excl_scan(const uint64_t (&v)[NV], uint64_t (&excl)[NV],
                                                 uint64_t (&total)[NV], uint64_t* sw, int lane,
                                                 int wid) {
@@ -255,7 +328,7 @@ __device__ __forceinline__ void block_excl_scan(const uint64_t (&v)[NV], uint64_
   for (int q = 0; q < NV; ++q) {
     uint64_t pre = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < TK_THREADS / WAVE; ++w) {
+    for (int w = 0; w < NT / WAVE; ++w) {
       const uint64_t t = sw[w * NV + q];
       pre += w < wid ? t : 0;
       all += t;
@@ -265,14 +338,16 @@ __device__ __forceinline__ void block_excl_scan(const uint64_t (&v)[NV], uint64_
   }
 }
 
-template <int PT>
-__global__ __launch_bounds__(TK_THREADS) void topk_kernel(
+template <int NT, int PT>
+__global__ __launch_bounds__(NT) void topk_kernel(
     const float* __restrict__ scores, int64_t ld, const int64_t* __restrict__ cand_off,
     const int32_t* __restrict__ seq_len, int max_len, int k, int32_t* __restrict__ out_idx,
     float* __restrict__ out_score, int out_ld, int32_t* __restrict__ cand_req) {
-  __shared__ int red[2][TK_THREADS / WAVE];
-  __shared__ uint64_t scan_w[(TK_THREADS / WAVE) * 5];
-  __shared__ __attribute__((aligned(16))) uint64_t sel[TAV2_K_MAX];
+  __shared__ int red[2][NT / WAVE];
+  __shared__ uint64_t scan_w[(NT / WAVE) * 5];
+  __shared__ __attribute__((aligned(16))) uint64_t sel[TAV2_K_MAX + BIN_MOST];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[NBINS];
+  __shared__ uint32_t bred[2 * NT / WAVE + 2];
 
   const int r = blockIdx.y;
   const int64_t n = cand_off[r] + blockIdx.x;
@@ -280,10 +355,11 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(
   if (cand_req && threadIdx.x == 0) cand_req[n] = r;   // the candidate's request, for the encoder
   const int L = min(seq_len[r], max_len);
   const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+  for (int b = tid; b < NBINS / 4; b += NT) reinterpret_cast<uint4*>(hist)[b] = make_uint4(0u, 0u, 0u, 0u);
   const int kk = k < L ? k : L;
   int32_t* oi = out_idx + n * out_ld;
   float* os = out_score + n * out_ld;
-  for (int p = kk + tid; p < k; p += TK_THREADS) {
+  for (int p = kk + tid; p < k; p += NT) {
     oi[p] = -1;
     os[p] = -__builtin_inff();
   }
@@ -293,7 +369,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(
   // that every load instruction reads 1 KB of consecutive scores per wave; rows
   // past L get key 0 (below every score)
   constexpr int NC = PT / 4;
-  constexpr int CH = TK_THREADS * 4;
+  constexpr int CH = NT * 4;
   const float* srow = scores + n * ld;
   uint32_t key[PT];   // key[4 c + u]: row CH c + 4 tid + u
 #pragma unroll
@@ -310,6 +386,26 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(
       for (int u = 0; u < 4; ++u) key[4 * c + u] = (r0 + u < L) ? score_key(srow[r0 + u]) : 0u;
     }
   }
+  {
+    // the kk-th best key is at least the kk-th best of the threads' largest keys, so the
+    // bins need not reach below the smallest of those when there are kk of them
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+      hi = max(hi, key[j]);
+      if (key[j]) lo = min(lo, key[j]);
+    }
+    const bool few = kk <= NT && 4 * (NT - 1) < L;   // every thread has a key
+    if (few) lo = hi;
+    block_min_max<NT>(lo, hi, bred);
+    __syncthreads();   // bred is reused
+    const uint32_t least = lo;
+    if (place_by_bins<NT, PT>(
+            [&](int e) { return key[e] >= least ? key[e] : 0u; },
+            [&](int e) { return (e / 4) * CH + tid * 4 + e % 4; }, lo, hi, kk, hist, bred, sel, oi, os))
+      return;
+    __syncthreads();   // bred, sel: nothing of them is read any more
+  }
 
   {
   // exhaustive: largest threshold t with count(key >= t) >= kk, one bit at a time
@@ -324,7 +420,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(
     __syncthreads();
     int tot = 0;
 #pragma unroll
-    for (int w = 0; w < TK_THREADS / WAVE; ++w) tot += red[b & 1][w];
+    for (int w = 0; w < NT / WAVE; ++w) tot += red[b & 1][w];
     if (tot >= kk) thr = probe;
   }
 
@@ -344,7 +440,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(
       word[1 + c / 4] += key[4 * c + u] == thr ? (uint64_t(1) << (16 * (c % 4))) : 0u;
     }
   uint64_t excl[NW + 1], total[NW + 1];
-  block_excl_scan<NW + 1>(word, excl, total, scan_w, lane, wid);
+  block_excl_scan<NW + 1, NT>(word, excl, total, scan_w, lane, wid);
   const int count_gt = int(total[0]);
   const int need_eq = kk - count_gt;
   int gpos = int(excl[0]);
@@ -371,7 +467,7 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(
   }
 
   // survivors are distinct under (key, -row): rank = number of survivors before it
-  for (int s = tid; s < kk; s += TK_THREADS) {
+  for (int s = tid; s < kk; s += NT) {
     const uint64_t me = sel[s];
     int rank = 0;
     // 8 independent LDS reads per iteration (the survivor count is not a
@@ -644,7 +740,7 @@ __global__ __launch_bounds__(TS_THREADS) void topk_stream_kernel(
       uint64_t e[1] = {0}, excl[1], total[1];
 #pragma unroll
       for (int u = 0; u < 4; ++u) e[0] += kv[u] == t ? 1u : 0u;
-      block_excl_scan<1>(e, excl, total, scan_w, lane, wid);
+      block_excl_scan<1, TS_THREADS>(e, excl, total, scan_w, lane, wid);
       int pos = eq_before + int(excl[0]);
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -696,6 +792,13 @@ hipError_t launch_scores(const tav2_seq& seq, const tav2_cands& c, float* scores
     dim3 grid(unsigned(cdiv(seq.max_len, SC_ROWS)), unsigned(cdiv(c.max_count, SC_CANDS)),
               unsigned(seq.num_requests));
     ProfScope prof("score_bf16", st);
+    if (int64_t(grid.x) * grid.y * grid.z * seq.d < SC_DIRECT) {
+      grid.y = unsigned(cdiv(c.max_count, SD_CANDS));
+      score_bf16_direct_kernel<<<grid, 256, 0, st>>>(
+          static_cast<const bf16_t*>(seq.emb), seq.offset, seq.len,
+          static_cast<const bf16_t*>(c.emb), c.offset, seq.d, seq.max_len, scores, ld);
+      return hipGetLastError();
+    }
     const size_t lds = size_t(SC_CANDS) * size_t(seq.d + SC_PAD) * 2;   // d <= 512: <= 133 KB
     static std::atomic<bool> lds_done[64] = {};
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(score_bf16_kernel),
@@ -732,16 +835,20 @@ hipError_t launch_topk(const tav2_seq& seq, const tav2_cands& c, const float* sc
                        hipStream_t st) {
   if (seq.num_requests == 0 || c.total == 0) return hipSuccess;
   dim3 grid(unsigned(c.max_count), unsigned(seq.num_requests));
-  const int per = int(cdiv(seq.max_len > 0 ? seq.max_len : 1, TK_THREADS));
   ProfScope prof("topk", st);
-#define TAV2_TOPK(PT) \
-  topk_kernel<PT><<<grid, TK_THREADS, 0, st>>>(scores, ld, c.offset, seq.len, seq.max_len, k, \
-                                               out_idx, out_score, out_ld, cand_req)
-  if (per <= 4) TAV2_TOPK(4);
-  else if (per <= 8) TAV2_TOPK(8);
-  else
-    topk_stream_kernel<<<grid, TS_THREADS, 0, st>>>(scores, ld, c.offset, seq.len, seq.max_len, k,
-                                                     out_idx, out_score, out_ld, cand_req);
+  const int L = seq.max_len;
+#define TAV2_TOPK(NT, PT) \
+  topk_kernel<NT, PT><<<grid, NT, 0, st>>>(scores, ld, c.offset, seq.len, L, k, out_idx, out_score, \
+                                           out_ld, cand_req)
+  if (L > 4096)
+    topk_stream_kernel<<<grid, TS_THREADS, 0, st>>>(scores, ld, c.offset, seq.len, L, k, out_idx,
+                                                     out_score, out_ld, cand_req);
+  else if (L <= 1024) TAV2_TOPK(256, 4);
+  else if (c.total <= TK_WIDE) {
+    if (L <= 2048) TAV2_TOPK(512, 4);
+    else TAV2_TOPK(512, 8);
+  } else if (L <= 2048) TAV2_TOPK(256, 8);
+  else TAV2_TOPK(256, 16);
 #undef TAV2_TOPK
   return hipGetLastError();
 }

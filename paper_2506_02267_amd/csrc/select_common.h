@@ -79,6 +79,18 @@ __device__ __forceinline__ uint64_t wave_and64(uint64_t x) {
   TAV2_DPP_STEPS(&, -1)
   return (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(v), 63))) << 32) | lo;
 }
+// Smallest / largest over the lanes, returned to every lane.
+#define TAV2_DPP_FN(F, ID)                                                                  \
+  v = F(v, uint32_t(__builtin_amdgcn_update_dpp(ID, int(v), 0x111, 0xf, 0xf, false)));  \
+  v = F(v, uint32_t(__builtin_amdgcn_update_dpp(ID, int(v), 0x112, 0xf, 0xf, false)));  \
+  v = F(v, uint32_t(__builtin_amdgcn_update_dpp(ID, int(v), 0x114, 0xf, 0xf, false)));  \
+  v = F(v, uint32_t(__builtin_amdgcn_update_dpp(ID, int(v), 0x118, 0xf, 0xf, false)));  \
+  v = F(v, uint32_t(__builtin_amdgcn_update_dpp(ID, int(v), 0x142, 0xa, 0xf, false)));  \
+  v = F(v, uint32_t(__builtin_amdgcn_update_dpp(ID, int(v), 0x143, 0xc, 0xf, false)));  \
+  return uint32_t(__builtin_amdgcn_readlane(int(v), 63));
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) { TAV2_DPP_FN(min, -1) }
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) { TAV2_DPP_FN(max, 0) }
+#undef TAV2_DPP_FN
 #undef TAV2_DPP_STEPS
 
 // One digit step of a descending radix select, done by a whole wave on a
@@ -196,6 +208,111 @@ __device__ __forceinline__ void place_by_rank(const uint64_t* sel, int kk, int32
     for (; t < kk; ++t) rank += sel[t] > me ? 1 : 0;
     oi[rank] = sel_row(me);
     os[rank] = key_score(sel_key(me));
+  }
+}
+
+// The kk best of a workgroup's keys to their places in the order, by bins.
+//
+// Keys are binned by (largest key - key) >> shift into 1024 bins of one width that
+// cover the keys' range; a value's rank is then the number of values in the bins
+// before its own plus its rank within the bin, so a bin of a few values takes a few
+// comparisons each, whatever kk is.  Only the values of bins up to the one that holds
+// the kk-th are moved.  (A radix select followed by counting, for each of the kk, how
+// many are larger, costs kk^2 comparisons: a search of 4000 candidates over 16384 rows
+// at kk = 512 took 234 us that way and takes 139, of 500 at kk = 1024 103 and 38, of
+// 1000 at kk = 256 60 and 51.  Over short rows, against a search for the kk-th key bit
+// by bit over the whole workgroup: 2800 candidates of 200 to 4000 rows at kk = 64, 62
+// and 31.)
+//
+// key(e), row(e): the thread's elements e = 0 .. PER - 1 (key(e) = 0: none).  kmin,
+// kmax: bounds of the workgroup's keys, the same for every thread.  hist (1024 words,
+// zeroed, 16-byte aligned) and red (NT / 64 + 2 words) are LDS scratch; sorted holds at
+// least kk + BIN_MOST - 1 values.  The caller synchronises before (hist is zero).
+// Returns false, with nothing written, when there is no kk-th value or its bin holds
+// more than BIN_MOST values (many equal scores): the caller then selects another way.
+constexpr int NBINS = 1024;
+constexpr int BIN_MOST = 512;
+template <int NT, int PER, class Key, class Row>
+__device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, uint32_t kmin,
+                                              uint32_t kmax, int kk, uint32_t* hist, uint32_t* red,
+                                              uint64_t* sorted, int32_t* oi, float* os) {
+  constexpr int NW = NT / WAVE, BPT = NBINS / NT;   // bins per thread
+  static_assert(BPT == 4 || BPT == 2, "one vector of bins per thread");
+  typedef uint32_t bins_t __attribute__((ext_vector_type(BPT)));
+  const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+  const uint32_t range = kmax - kmin;
+  const int bits = range ? 32 - __builtin_clz(range) : 0, shift = bits > 10 ? bits - 10 : 0;
+  auto bin = [&](uint32_t k) { return (kmax - k) >> shift; };
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (key(e)) atomicAdd(&hist[bin(key(e))], 1u);
+  __syncthreads();
+  // exclusive prefix over the bins, in place; the bin that holds the kk-th value
+  const bins_t h = reinterpret_cast<const bins_t*>(hist)[tid];
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < BPT; ++i) sum += h[i];
+  const uint32_t incl = wave_incl_sum(sum);
+  if (lane == WAVE - 1) red[wid] = incl;
+  if (tid == 0) red[NW + 1] = ~0u;   // (fewer than kk keys: nothing is placed)
+  __syncthreads();
+  uint32_t at = incl - sum;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) at += w < wid ? red[w] : 0u;
+  const uint32_t need = uint32_t(kk);
+  bins_t start;
+#pragma unroll
+  for (int i = 0; i < BPT; ++i) {
+    start[i] = at;
+    if (at < need && need <= at + h[i]) {
+      red[NW] = at + h[i];                 // values up to that bin's end
+      red[NW + 1] = h[i] > uint32_t(BIN_MOST) ? ~0u : uint32_t(BPT * tid + i);
+    }
+    at += h[i];
+  }
+  reinterpret_cast<bins_t*>(hist)[tid] = start;
+  __syncthreads();
+  const int total = int(red[NW]);
+  const uint32_t last = red[NW + 1];
+  if (last == ~0u) return false;
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (key(e)) {
+      const uint32_t b = bin(key(e));
+      if (b <= last) sorted[atomicAdd(&hist[b], 1u)] = sel_value(key(e), row(e));
+    }
+  __syncthreads();   // hist[b] is now the end of bin b <= last, and the start of the next
+  for (int i = tid; i < total; i += NT) {
+    const uint64_t me = sorted[i];
+    const uint32_t b = bin(sel_key(me));
+    const int s0 = b ? int(hist[b - 1]) : 0, s1 = int(hist[b]);
+    int rank = s0;
+    for (int j = s0; j < s1; ++j) rank += sorted[j] > me ? 1 : 0;
+    if (rank < kk) {
+      oi[rank] = sel_row(me);
+      os[rank] = key_score(sel_key(me));
+    }
+  }
+  return true;
+}
+
+// Workgroup-wide largest (and smallest) of a value; red: NT / 64 words each.  Ends
+// with a barrier.
+template <int NT>
+__device__ __forceinline__ void block_min_max(uint32_t& lo, uint32_t& hi, uint32_t* red) {
+  constexpr int NW = NT / WAVE;
+  const int lane = threadIdx.x % WAVE, wid = threadIdx.x / WAVE;
+  lo = wave_min_u(lo);
+  hi = wave_max_u(hi);
+  if (lane == 0) {
+    red[wid] = lo;
+    red[NW + wid] = hi;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    lo = min(lo, red[w]);
+    hi = max(hi, red[NW + w]);
   }
 }
 

@@ -683,16 +683,21 @@ __global__ __launch_bounds__(256) void fsel_filter_i8(FusedArgs A) {
 }
 
 // ---------------------------------------------------------------- 4. select
-// One workgroup per candidate: the k best of its survivors (a radix select of
-// the k-th largest, the values at or above it, placed by rank), or the queue.
+// One workgroup per candidate: the k best of its survivors, placed by bins (where
+// many survivors have equal scores: a radix select of the k-th largest, the values at
+// or above it, placed by counting), or the queue.
 constexpr int FT_THREADS = 256;
+__host__ __device__ __forceinline__ size_t fsel_select_lds(int cap, int k) {
+  return (size_t(cap) + align_up(size_t(k), 2)) * 8;   // survivors, selected
+}
 __global__ __launch_bounds__(FT_THREADS) void fsel_select(FusedArgs A, int32_t* __restrict__ out_idx,
                                                           float* __restrict__ out_score,
                                                           int32_t* __restrict__ cand_req) {
-  __shared__ uint64_t vals[FS_CAP_MAX];
-  __shared__ __attribute__((aligned(16))) uint64_t sel[TAV2_K_MAX];
-  __shared__ __attribute__((aligned(16))) uint32_t hist[3 * 256];
+  extern __shared__ __attribute__((aligned(16))) uint8_t ft_smem[];
+  uint64_t* vals = reinterpret_cast<uint64_t*>(ft_smem);   // [cap]
+  __shared__ __attribute__((aligned(16))) uint32_t hist[NBINS];
   __shared__ uint64_t red[2 * FT_THREADS / WAVE];
+  __shared__ uint32_t bred[2 * FT_THREADS / WAVE + 2];
   __shared__ int nsel;
   const int r = blockIdx.y;
   const int64_t n = A.cand_off[r] + blockIdx.x;
@@ -719,19 +724,33 @@ __global__ __launch_bounds__(FT_THREADS) void fsel_select(FusedArgs A, int32_t* 
     return;
   }
   const int m = int(cnt);
-  {   // every load of the list in flight before the first store
-    constexpr int PER = FS_CAP_MAX / FT_THREADS;
-    uint64_t v[PER];
+  constexpr int PER = FS_CAP_MAX / FT_THREADS;
+  uint64_t v[PER];
+  uint32_t lo = ~0u, hi = 0u;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int i = tid + FT_THREADS * u;
-      if (i < m) v[u] = A.surv[n * A.cap + i];
-    }
+  for (int u = 0; u < PER; ++u) {
+    const int i = tid + FT_THREADS * u;
+    v[u] = 0;
+    if (i < m) v[u] = A.surv[n * A.cap + i];
+  }
+  reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int i = tid + FT_THREADS * u;
-      if (i < m) vals[i] = v[u];
+  for (int u = 0; u < PER; ++u)
+    if (v[u]) {
+      lo = min(lo, sel_key(v[u]));
+      hi = max(hi, sel_key(v[u]));
     }
+  block_min_max<FT_THREADS>(lo, hi, bred);
+  __syncthreads();   // bred is reused
+  if (place_by_bins<FT_THREADS, PER>([&](int e) { return sel_key(v[e]); },
+                                     [&](int e) { return sel_row(v[e]); }, lo, hi, kk, hist, bred,
+                                     vals, oi, os))
+    return;
+  uint64_t* sel = vals + A.cap;   // [k]
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = tid + FT_THREADS * u;
+    if (i < m) vals[i] = v[u];
   }
   if (tid == 0) nsel = 0;
   const uint64_t pre = radix_select48<FT_THREADS>(vals, m, kk, hist, red);
@@ -991,7 +1010,7 @@ hipError_t launch_select_fused(const tav2_seq& seq, const tav2_cands& c, int k,
   }
   {
     ProfScope prof("nn_select", st);
-    fsel_select<<<dim3(unsigned(c.max_count), R), FT_THREADS, 0, st>>>(A, out_idx, out_score,
+    fsel_select<<<dim3(unsigned(c.max_count), R), FT_THREADS, fsel_select_lds(A.cap, k), st>>>(A, out_idx, out_score,
                                                                         cand_req);
     if ((e = hipGetLastError())) return e;
   }

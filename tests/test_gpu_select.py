@@ -203,3 +203,48 @@ def test_repeated_runs_and_streams_are_bitwise_identical():
         st.synchronize()
     for i, s in outs[1:]:
         assert torch.equal(i, outs[0][0]) and torch.equal(s, outs[0][1])
+
+
+@pytest.mark.parametrize("N,L,k", [
+    (3, 1, 1), (3, 40, 64), (5, 1020, 256), (5, 1021, 256), (5, 1021, 257), (5, 1024, 1000),
+    (5, 1025, 64), (600, 1025, 64), (5, 2044, 512), (5, 2045, 512), (600, 2049, 700),
+    (5, 4096, 1024), (600, 4096, 256)])
+@pytest.mark.parametrize("ties", ["none", "some", "all"])
+def test_short_row_bins(N, L, k, ties):
+    """Rows of up to 4096 keys, placed by bins: every workgroup shape, key counts around
+    what a thread's four rows cover, k around the thread count and above the row; scores
+    with few ties, with a third of the rows equal (a bin past its limit), and all equal
+    (the bitwise search)."""
+    print(f"short rows N={N} L={L} k={k} ties={ties}", flush=True)
+    w = synth.scaled(synth.SINGLE, L=L, N=N, k=k, d=64)
+    inp = synth.make_inputs(w, seed=L + k)
+    if ties != "none":
+        n = L if ties == "all" else max(1, L // 3)
+        pick = np.random.default_rng(L).permutation(L)[:n]
+        inp.seq.emb[pick] = inp.seq.emb[0]
+    seq, _, cands = upload(inp)
+    idx, score = T.nn_select(seq, cands, k)
+    torch.cuda.synchronize()
+    ids = np.unique(np.r_[np.arange(min(N, 8)), np.arange(0, N, 61), N - 1])
+    ref_i, ref_s = oracle_select(inp, k, ids=ids)
+    assert_select_equal(idx, score, ref_i, ref_s, ids=ids)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+@pytest.mark.parametrize("copies,k", [(300, 64), (700, 64), (700, 1024)])
+def test_long_row_bins_with_equal_scores(dtype, copies, k):
+    """Long rows whose best survivors include many equal scores: within the bins' limit
+    (300 copies of one row) and past it (700: the radix select)."""
+    print(f"long rows {dtype} copies={copies} k={k}", flush=True)
+    base = synth.SELECT_I8 if dtype == "i8" else synth.SINGLE
+    w = synth.scaled(base, L=9000, N=6, k=k, d=64, tie_frac=0.0)
+    inp = synth.make_inputs(w, seed=copies)
+    rows = np.random.default_rng(copies).permutation(9000)[:copies]
+    c0 = inp.cand[0]
+    best = int(np.argmax(inp.seq.emb.astype(np.float64) @ c0))
+    inp.seq.emb[rows] = inp.seq.emb[best]
+    seq, _, cands = upload(inp)
+    idx, score = T.nn_select(seq, cands, k)
+    torch.cuda.synchronize()
+    ref_i, ref_s = oracle_select(inp, k)
+    assert_select_equal(idx, score, ref_i, ref_s)
