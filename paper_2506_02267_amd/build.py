@@ -46,6 +46,7 @@ def compile_flags():
 # must round correctly (the compiler's default for HIP, stated explicitly).
 EXTRA_FLAGS = {"encoder_fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_fused_unmasked.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "encoder_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm",
                                      "-amdgpu-sched-strategy=max-ilp"],
                "select.hip": ["-fhip-fp32-correctly-rounded-divide-sqrt"],

@@ -1,19 +1,26 @@
 // float32 encoder for small shapes (T <= 64, d_model <= 128, FFN <= 512, d <=
 // 256): one workgroup per candidate runs Eq. 4's feature encoding, the causal
-// post-LN layers and the linear + max-pool head (Sec. 3.2.2) with fp32 FMA.
-// Only the valid prefix of each candidate is computed: no valid position sees
-// padding (under the causal mask, or in the unmasked mode, where a position sees
-// the whole valid prefix).
+// post-LN layers and the linear + max-pool head (Sec. 3.2.2) on the fp32 matrix
+// instructions.  Only the valid prefix of each candidate is computed: no valid
+// position sees padding (under the causal mask, or in the unmasked mode, where a
+// position sees the whole valid prefix).
 //
-// Every product is an LDS-resident GEMM Y[r][c] = sum_k A[r][k] B[k][c] with one
-// register tile per thread: rows w + 4 i of wave w (one 16-byte broadcast read of
-// A per 4 k), columns lane + 64 j (consecutive LDS words of B).  Weight matrices
-// stream from memory in chunks of 16 k (coalesced along k) into a transposed LDS
-// chunk; Q, V, the token rows and the FFN hidden chunk share one LDS region, K is
-// kept transposed (keys as columns) for the score product, and the attention
-// probabilities go through their own buffer into the P V product.  Rows of a
-// product belong to one wave, so LayerNorm and softmax reduce across the lanes of
-// a wave (DPP) on registers.
+// A wave owns a tile of 16 tokens from Eq. 4 to the head.  Products are taken
+// transposed (weights as the A operand of 16x16x4 MFMAs): lane l then holds token
+// l % 16 and features 16 f + 4 g + i (g = l / 16) in register i of accumulator f, and
+// register s of accumulator f is, as it stands, the B operand of a step over the
+// features 16 f + {s, 4 + s, 8 + s, 12 + s}.  The matching A operands of the four steps
+// are the four floats W[row][16 f + 4 g ..], one 16-byte load per lane straight from the
+// row-major matrix.  So activations stay in registers through every product, weights
+// pass through neither LDS nor a barrier, and only K and V^T are shared between the
+// waves (two barriers a layer).
+//
+// What bounds it: a candidate's chain of products on one SIMD per 16 tokens (32 cycles a
+// step) and the latency of the weight stream, which is kept PF row tiles ahead, across
+// the products' ends.  16 candidates of 32 positions (d_model 64, FFN 128, one layer):
+// a search and 23 us, where LDS-staged products on the vector units (a register tile
+// per thread, two LDS reads a k step, a weight chunk's barriers) took 74; 1600 of 60
+// positions, two layers, 350 us with the search (1379).
 #include "common.h"
 #include "internal.h"
 #include "token_source.h"
@@ -23,468 +30,351 @@
 namespace tav2 {
 namespace f32e {
 
-constexpr int NT = 256;
-constexpr int NW = NT / WAVE;
 constexpr int MAX_LAYERS = 8;
-constexpr int KC_MAX = 32;           // k per staged weight chunk at most (16 or 32)
-constexpr int NB = 128;              // output columns per weight product at most
-constexpr int WS_LD = NB + 4;        // chunk row stride (== 4 mod 64: conflict-free stores)
-constexpr int FC = 128;              // FFN hidden units per chunk
-constexpr int SPT = KC_MAX * NB / NT;   // staged weight words per thread at most
-constexpr int LDS_MAX = 163840 - F32_MAX_T * int(sizeof(void*));   // dynamic LDS bytes
+constexpr int TT = 16;               // tokens per wave
+constexpr int MAX_NW = F32_MAX_T / TT;
+constexpr int LDS_MAX = 163840 - F32_MAX_T * int(sizeof(void*));   // of the accepted shapes
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 mma(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
 struct Args {
   TokenSource s;
   const float* cand;
-  int d, dm, H, ffn, n_layers;
+  int d, dm, dh, H, ffn, n_layers;
   const float *W_in, *b_in, *E_act, *E_time, *E_pos, *W_pool, *b_pool;
   tav2_layer layers[MAX_LAYERS];
   float* out;
   int unmasked;   // 1: every valid position sees every valid position
-  // LDS plan (floats)
-  int ldx, ldq, ldk, ldp, lde, ldh;
-  int kc_shift;   // log2 of k per weight chunk: the largest chunk the LDS has room for
-  int o_x, o_q, o_k, o_p, o_w, o_cv, o_red, o_meta, lds_floats;
+  int ldv;        // row stride of V^T in LDS (floats): positions rounded up to 16, + 4
 };
 
 __host__ __device__ inline int round4(int x) { return (x + 3) / 4 * 4; }
 
-__host__ inline void plan(Args& a, int T) {
-  a.ldx = a.dm + 4;
-  a.ldq = 2 * a.dm + 4;                   // [Q | V] rows
-  a.ldk = T % 2 ? T + 2 : T + 1;          // K^T rows (odd: conflict-free transposed stores)
-  a.ldp = round4(T) + 4;
-  a.lde = a.d + 4;
-  a.ldh = FC + 4;
-  int off = 0;
-  auto take = [&](int floats) {
-    const int at = off;
-    off += round4(floats);
-    return at;
-  };
-  const int rows = round4(T);
-  a.o_x = take(rows * a.ldx);
-  int region = rows * a.ldq;
-  region = region > rows * a.lde ? region : rows * a.lde;
-  region = region > rows * a.ldh ? region : rows * a.ldh;
-  a.o_q = take(region);
-  a.o_k = take(a.dm * a.ldk);
-  a.o_p = take(rows * a.ldp);
-  a.o_cv = take(a.dm);
-  a.o_red = take(NW * a.dm);
-  a.o_meta = take(2 * F32_MAX_T);         // act, time of each row
-  a.kc_shift = 4;
-  for (int sh = 5; sh > 4; --sh)
-    if ((off + (1 << sh) * WS_LD) * 4 <= LDS_MAX) {
-      a.kc_shift = sh;
-      break;
-    }
-  a.o_w = take((1 << a.kc_shift) * WS_LD);
-  a.lds_floats = off;
-}
-
-// Wave-wide float sum / max, returned to every lane (DPP row shifts and row
-// broadcasts; lane 63 ends with the result).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_f(float v, float id) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(id), __float_as_int(v), CTRL,
-                                                    ROW_MASK, 0xf, false));
-}
-#define F32E_REDUCE(OP, ID)                       \
-  v = OP(v, dpp_f<0x111, 0xf>(v, ID));            \
-  v = OP(v, dpp_f<0x112, 0xf>(v, ID));            \
-  v = OP(v, dpp_f<0x114, 0xf>(v, ID));            \
-  v = OP(v, dpp_f<0x118, 0xf>(v, ID));            \
-  v = OP(v, dpp_f<0x142, 0xa>(v, ID));            \
-  v = OP(v, dpp_f<0x143, 0xc>(v, ID));            \
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-__device__ __forceinline__ float f_add(float a, float b) { return a + b; }
-__device__ __forceinline__ float f_max(float a, float b) { return vmax(a, b); }
-__device__ __forceinline__ float wave_sum_f(float v) { F32E_REDUCE(f_add, 0.f) }
-__device__ __forceinline__ float wave_max_f(float v) { F32E_REDUCE(f_max, -__builtin_inff()) }
-#undef F32E_REDUCE
-
-template <int RI, int CJ>
-__device__ __forceinline__ void zero(float (&acc)[RI][CJ]) {
-#pragma unroll
-  for (int i = 0; i < RI; ++i)
-#pragma unroll
-    for (int j = 0; j < CJ; ++j) acc[i][j] = 0.f;
-}
-
-// acc[i][j] += sum_{k < K} A[r][k] B[k][c] for rows r = w + 4 i (RI of them:
-// those at or past `rows` repeat the last row and are discarded by the caller)
-// and columns c = lane + 64 j, with A and B in LDS (B: row stride ldb; columns
-// past the product's width read whatever follows in LDS and are discarded too).
-// K is a multiple of 4 and A's rows 16-byte aligned.  No branch inside: every
-// load of a k step is in flight at once.
-template <int RI, int CJ>
-__device__ __forceinline__ void gemm_lds(float (&acc)[RI][CJ], const float* A, int lda, int rows,
-                                         int K, const float* B, int ldb) {
-  const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-  const float* ar[RI];
-#pragma unroll
-  for (int i = 0; i < RI; ++i) {
-    const int r = w + NW * i;
-    ar[i] = A + (r < rows ? r : rows - 1) * lda;
-  }
-  const float* bc = B + lane;
-  for (int k = 0; k < K; k += 4) {
-    float b[4][CJ];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int j = 0; j < CJ; ++j) b[e][j] = bc[(k + e) * ldb + WAVE * j];
-    float4 av[RI];
-#pragma unroll
-    for (int i = 0; i < RI; ++i) av[i] = *reinterpret_cast<const float4*>(ar[i] + k);
-#pragma unroll
-    for (int i = 0; i < RI; ++i)
-#pragma unroll
-      for (int j = 0; j < CJ; ++j) {
-        float t = acc[i][j];
-        t = fmaf(av[i].x, b[0][j], t);
-        t = fmaf(av[i].y, b[1][j], t);
-        t = fmaf(av[i].z, b[2][j], t);
-        t = fmaf(av[i].w, b[3][j], t);
-        acc[i][j] = t;
-      }
-  }
-}
-
-// One staged chunk of a weight matrix W ([N][K] with row stride ldw, N <= NB) in
-// registers: the thread's 16-byte pieces (4 consecutive k of one column) e = tid +
-// NT q, column e / (kc / 4), k 4 (e % (kc / 4)).  K, ldw and the column offsets are
-// multiples of 4, so a piece is all inside or all past K.
-struct WChunk {
-  float4 v[SPT / 4];
+// A matrix that a phase multiplies by: rows [0, rows) and columns [0, cols) of W (row
+// stride ld), everything past them zero; cols and ld are multiples of 4, W is 16-byte
+// aligned where the accepted shapes have it so (rows are whole 16-byte groups).
+struct Mat {
+  const float* W;
+  int ld, rows, cols;
 };
-__device__ __forceinline__ void w_fetch(WChunk& st, const float* __restrict__ W, int ldw, int N,
-                                        int K, int k0, int ks) {
-  const int tid = threadIdx.x, ks4 = ks - 2, spt = ((1 << ks) * NB) / (4 * NT);
+// Row tile r's operands over the DT k-tiles.
+template <int DT>
+__device__ __forceinline__ void load_rows(f32x4 (&a)[DT], const Mat& m, int r) {
+  const int lane = threadIdx.x % WAVE, row = 16 * r + lane % 16, k0 = 4 * (lane / 16);
+  const float* p = m.W + int64_t(row) * m.ld + k0;
 #pragma unroll
-  for (int q = 0; q < SPT / 4; ++q) {
-    const int e = tid + NT * q, c = e >> ks4, kk = (e & ((1 << ks4) - 1)) * 4;
-    st.v[q] = (q < spt && c < N && k0 + kk < K)
-                  ? *reinterpret_cast<const float4*>(W + c * ldw + k0 + kk)
-                  : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int f = 0; f < DT; ++f)
+    a[f] = row < m.rows && 16 * f + k0 < m.cols ? *reinterpret_cast<const f32x4*>(p + 16 * f)
+                                                : f32x4{0.f, 0.f, 0.f, 0.f};
+}
+// The weight stream: PF row tiles in flight.  A phase has DT row tiles; its last PF
+// iterations load the first PF row tiles of the next phase.
+template <int DT, int PF>
+struct Ring {
+  f32x4 a[PF][DT];
+};
+template <int DT, int PF>
+__device__ __forceinline__ void prime(Ring<DT, PF>& q, const Mat& m) {
+#pragma unroll
+  for (int r = 0; r < PF; ++r) load_rows<DT>(q.a[r], m, r);
+}
+// acc[r] += (rows 16 r .. of cur) x; TOK: the other way round (lane holds feature 16 r +
+// l % 16 of tokens 4 g + i).  The product is summed apart from acc, in two halves: added
+// step by step onto the residual it would round at the residual's size every time
+// (errors against 64 bits 3.3e-7 instead of 1.9e-7; the vector units' sums had 2.2e-7).
+template <int DT, int PF, bool TOK = false>
+__device__ __forceinline__ void phase(Ring<DT, PF>& q, f32x4 (&acc)[DT], const f32x4 (&x)[DT],
+                                      const Mat& cur, const Mat& next) {
+#pragma unroll
+  for (int r = 0; r < DT; ++r) {
+    f32x4 part[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int f = 0; f < DT; ++f)
+        part[f % 2] = TOK ? mma(x[f][s], q.a[r % PF][f][s], part[f % 2])
+                          : mma(q.a[r % PF][f][s], x[f][s], part[f % 2]);
+    acc[r] += part[0] + part[1];
+    load_rows<DT>(q.a[r % PF], r + PF < DT ? cur : next, r + PF < DT ? r + PF : r + PF - DT);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// acc[i][j] += sum_{k < K} A[r][k] W[c][k]: A in LDS, W staged through the LDS
-// chunk Ws, 2^ks k at a time (coalesced along k, stored transposed), each chunk's
-// loads in flight while the one before is multiplied.  Starts with a barrier
-// (earlier readers of Ws and of anything the caller writes before calling are
-// done) and ends without one.
-template <int RI, int CJ>
-__device__ __forceinline__ void gemm_w(float (&acc)[RI][CJ], const float* A, int lda, int rows,
-                                       int K, const float* __restrict__ W, int ldw, int N,
-                                       float* Ws, int ks) {
-  const int tid = threadIdx.x;
-  WChunk st;
-  w_fetch(st, W, ldw, N, K, 0, ks);
-  const int kc_full = 1 << ks, spt = (kc_full * NB) / (4 * NT), ks4 = ks - 2;
-  for (int k0 = 0; k0 < K; k0 += kc_full) {
-    __syncthreads();
+// v[4 f + i] of a feature vector for the lane's features (zero past dm).
+template <int DT>
+__device__ __forceinline__ void load_vec(f32x4 (&v)[DT], const float* p, int n) {
+  const int k0 = 4 * (threadIdx.x % WAVE / 16);
 #pragma unroll
-    for (int q = 0; q < SPT / 4; ++q) {
-      const int e = tid + NT * q, c = e >> ks4, kk = (e & ((1 << ks4) - 1)) * 4;
-      if (q < spt && c < N) {
-        Ws[kk * WS_LD + c] = st.v[q].x;
-        Ws[(kk + 1) * WS_LD + c] = st.v[q].y;
-        Ws[(kk + 2) * WS_LD + c] = st.v[q].z;
-        Ws[(kk + 3) * WS_LD + c] = st.v[q].w;
-      }
-    }
-    __syncthreads();
-    if (k0 + kc_full < K) w_fetch(st, W, ldw, N, K, k0 + kc_full, ks);
-    const int kc = K - k0 < kc_full ? K - k0 : kc_full;
-    gemm_lds<RI, CJ>(acc, A + k0, lda, rows, kc, Ws, WS_LD);
-  }
+  for (int f = 0; f < DT; ++f)
+    v[f] = 16 * f + k0 < n ? *reinterpret_cast<const f32x4*>(p + 16 * f + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
 }
-
-// Post-LN sublayer end on registers: X[r] <- LayerNorm(acc[r] + bias + X[r]).
-// The row's dm values sit in the lanes of one wave.
-template <int RI>
-__device__ __forceinline__ void add_norm(float (&acc)[RI][2], float* X, int ldx, int rows, int dm,
-                                         const float* __restrict__ bias,
-                                         const float* __restrict__ g,
-                                         const float* __restrict__ be) {
-  const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-  float bv[2], gv[2], ev[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int c = lane + WAVE * j;
-    bv[j] = c < dm ? bias[c] : 0.f;
-    gv[j] = c < dm ? g[c] : 0.f;
-    ev[j] = c < dm ? be[c] : 0.f;
-  }
+// x <- LayerNorm(x) over the dm features of the lane's token (padding features stay 0).
+template <int DT>
+__device__ __forceinline__ void layer_norm(f32x4 (&x)[DT], const f32x4 (&gain)[DT],
+                                           const f32x4 (&off)[DT], int dm) {
+  const int k0 = 4 * (threadIdx.x % WAVE / 16);
   const float inv = 1.f / float(dm);
+  float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < RI; ++i) {
-    const int r = w + NW * i;
-    if (r < rows) {
-      float y[2];
-      float s = 0.f;
+  for (int f = 0; f < DT; ++f) s += (x[f][0] + x[f][1]) + (x[f][2] + x[f][3]);
+  const float mu = xsum32(xsum16(s)) * inv;
+  float v = 0.f;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int c = lane + WAVE * j;
-        y[j] = c < dm ? acc[i][j] + bv[j] + X[r * ldx + c] : 0.f;
-        s += y[j];
-      }
-      const float mu = wave_sum_f(s) * inv;
-      float q = 0.f;
+  for (int f = 0; f < DT; ++f) {
+    const bool in = 16 * f + k0 < dm;
+    float t = 0.f;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int c = lane + WAVE * j;
-        const float t = c < dm ? y[j] - mu : 0.f;
-        q = fmaf(t, t, q);
-      }
-      const float rs = rsqrtf(wave_sum_f(q) * inv + 1e-5f);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int c = lane + WAVE * j;
-        if (c < dm) X[r * ldx + c] = (y[j] - mu) * rs * gv[j] + ev[j];
-      }
+    for (int i = 0; i < 4; ++i) {
+      x[f][i] = in ? x[f][i] - mu : 0.f;
+      t = fmaf(x[f][i], x[f][i], t);
     }
+    v += t;
   }
+  const float rs = rsqrtf(xsum32(xsum16(v)) * inv + 1e-5f);
+#pragma unroll
+  for (int f = 0; f < DT; ++f)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[f][i] = x[f][i] * rs * gain[f][i] + off[f][i];
 }
 
-// RI = rows per wave: positions up to 4 RI.
-template <int RI>
-__global__ __launch_bounds__(NT) void encode_f32_kernel(Args a) {
+// DT: tiles of 16 features (d_model <= 16 DT); PF: row tiles of weights in flight.
+template <int DT, int PF>
+__global__ __launch_bounds__(MAX_NW* WAVE) void encode_f32_kernel(Args A) {
+  constexpr int DP = 16 * DT, LDK = DP + 4;
+  static_assert(DT % PF == 0, "whole rounds of the ring");
   extern __shared__ __attribute__((aligned(16))) float lds[];
   const int64_t n = blockIdx.x;
-  const int tid = threadIdx.x, w = tid / WAVE, lane = tid % WAVE;
-  const int dm = a.dm, d = a.d;
-  const int dh = dm / a.H;
-  const int Tv = token_valid_len(a.s, n);
-  float* out = a.out + n * 2 * dm;
+  const int tid = threadIdx.x, w = tid / WAVE, lane = tid % WAVE, nw = blockDim.x / WAVE;
+  const int c16 = lane % 16, g = lane / 16;
+  const int dm = A.dm, d = A.d, dh = A.dh;
+  const int Tv = token_valid_len(A.s, n);
+  float* out = A.out + n * 2 * dm;
   if (Tv == 0) {
-    for (int c = tid; c < 2 * dm; c += NT) out[c] = 0.f;
+    for (int c = tid; c < 2 * dm; c += blockDim.x) out[c] = 0.f;
     return;
   }
-  float* X = lds + a.o_x;
-  float* QV = lds + a.o_q;   // [Q | V], the token rows, the FFN hidden chunk
-  float* Kt = lds + a.o_k;
-  float* P = lds + a.o_p;
-  float* Ws = lds + a.o_w;
-  float* cvec = lds + a.o_cv;
-  float* red = lds + a.o_red;
-  int* meta = reinterpret_cast<int*>(lds + a.o_meta);   // act [64], time [64]
-  const float** rowp = nullptr;
-  __shared__ const float* rows_ptr[F32_MAX_T];
-  rowp = rows_ptr;
-
-  // ---- Eq. 4 with early fusion: [e_p ; e_c] W_in^T + b_in + side tables
-  if (tid < Tv) {
-    const TokenRef t = resolve_token(a.s, n, tid, d * 4);
-    rowp[tid] = reinterpret_cast<const float*>(t.emb);
-    meta[tid] = t.act;
-    meta[F32_MAX_T + tid] = t.time;
-  }
-  {   // candidate half, once: cvec[c] = b_in[c] + sum_k cand[k] W_in[c][d + k]
-      // (wave w: columns w + 4 q, 8 at a time; lanes over k)
-    const float* cv = a.cand + n * d;
-    float cq[F32_MAX_D / WAVE];
+  float* Ks = lds;                          // [16 nw][LDK]
+  float* Vt = Ks + 16 * nw * LDK;           // [DP][ldv]
+  float* pool = Vt + DP * A.ldv;            // [nw][DP]
+  const int t0 = TT * w, p = t0 + c16;      // the wave's first position, the lane's
+  const bool live = t0 < Tv;                // wave-uniform
+  // token columns of W_in, then the candidate's, 16 DT at a time
+  const int nc = (d + DP - 1) / DP;
+  auto in_mat = [&](int c) {   // chunk c: of the token half, then of the candidate half
+    const int k0 = (c < nc ? c : c - nc) * DP;
+    return Mat{A.W_in + (c < nc ? 0 : d) + k0, 2 * d, dm, d - k0};
+  };
+  auto layer_mat = [&](const void* W, int row0, int rows, int cols, int ld, int k0) {
+    return Mat{static_cast<const float*>(W) + int64_t(row0) * ld + k0, ld, rows, cols};
+  };
+  Ring<DT, PF> q;
+  f32x4 x[DT];
+  if (live) {
+    prime(q, in_mat(0));
+    TokenRef t{nullptr, 0, 0};
+    if (p < Tv) t = resolve_token(A.s, n, p, d * 4);
+    // ---- Eq. 4 with early fusion: [e_p ; e_c] W_in^T + b_in + side tables
+    f32x4 ta[DT], tp[DT];
+    load_vec<DT>(x, A.b_in, dm);
+    load_vec<DT>(ta, A.E_act + t.act * dm, dm);
+    load_vec<DT>(tp, A.E_pos + (p < Tv ? p : Tv - 1) * dm, dm);
 #pragma unroll
-    for (int t = 0; t < F32_MAX_D / WAVE; ++t) {
-      const int k = lane + WAVE * t;
-      cq[t] = k < d ? cv[k] : 0.f;
+    for (int f = 0; f < DT; ++f) x[f] += ta[f] + tp[f];
+    if (A.E_time) {
+      load_vec<DT>(ta, A.E_time + t.time * dm, dm);
+#pragma unroll
+      for (int f = 0; f < DT; ++f) x[f] += ta[f];
     }
-    for (int c0 = w; c0 < dm; c0 += NW * 8) {
-      float sv[8];
+    const float* cv = A.cand + n * d;
+    for (int c = 0; c < 2 * nc; ++c) {
+      const int k0 = (c < nc ? c : c - nc) * DP;
+      const float* src = c < nc ? reinterpret_cast<const float*>(t.emb) : cv;
+      f32x4 e[DT];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int c = c0 + NW * q;
-        const float* wr = a.W_in + int64_t(c < dm ? c : 0) * 2 * d + d;
-        float s = 0.f;
-#pragma unroll
-        for (int t = 0; t < F32_MAX_D / WAVE; ++t) {
-          const int k = lane + WAVE * t;
-          if (k < d) s = fmaf(cq[t], wr[k], s);
-        }
-        sv[q] = s;
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int c = c0 + NW * q;
-        const float s = wave_sum_f(sv[q]);
-        if (lane == 0 && c < dm) cvec[c] = s + a.b_in[c];
-      }
-    }
-  }
-  __syncthreads();
-  for (int e0 = 0; e0 < Tv * d; e0 += NT * 8) {   // token rows into LDS (zeros for padding)
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = e0 + tid + NT * q;
-      const int r = e / d, k = e % d;
-      v[q] = 0.f;
-      if (e < Tv * d && rowp[r]) v[q] = rowp[r][k];
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = e0 + tid + NT * q;
-      if (e < Tv * d) QV[(e / d) * a.lde + e % d] = v[q];
-    }
-  }
-  {
-    float acc[RI][2];
-    zero<RI, 2>(acc);
-    gemm_w<RI, 2>(acc, QV, a.lde, Tv, d, a.W_in, 2 * d, dm, Ws, a.kc_shift);
-#pragma unroll
-    for (int i = 0; i < RI; ++i) {
-      const int r = w + NW * i;
-      if (r < Tv) {
-        const int act = meta[r], tm = meta[F32_MAX_T + r];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int c = lane + WAVE * j;
-          if (c < dm) {
-            float x = acc[i][j] + cvec[c] + a.E_act[act * dm + c] + a.E_pos[r * dm + c];
-            if (a.E_time) x += a.E_time[tm * dm + c];
-            X[r * a.ldx + c] = x;
-          }
-        }
-      }
+      for (int f = 0; f < DT; ++f)
+        e[f] = src && k0 + 16 * f + 4 * g < d
+                   ? *reinterpret_cast<const f32x4*>(src + k0 + 16 * f + 4 * g)
+                   : f32x4{0.f, 0.f, 0.f, 0.f};
+      phase(q, x, e, in_mat(c),
+            c + 1 < 2 * nc ? in_mat(c + 1) : layer_mat(A.layers[0].W_qkv, 0, dm, dm, dm, 0));
     }
   }
 
   const float scale = 1.f / sqrtf(float(dh));
-  const int Kr = round4(Tv);   // keys of the P V product, zero-padded to a multiple of 4
-  for (int li = 0; li < a.n_layers; ++li) {
-    const tav2_layer& L = a.layers[li];
-    const float* Wqkv = static_cast<const float*>(L.W_qkv);
-    // ---- Q, K (transposed), V
-    for (int part = 0; part < 3; ++part) {
-      float acc[RI][2];
-      zero<RI, 2>(acc);
-      gemm_w<RI, 2>(acc, X, a.ldx, Tv, dm, Wqkv + int64_t(part) * dm * dm, dm, dm, Ws, a.kc_shift);
-#pragma unroll
-      for (int i = 0; i < RI; ++i) {
-        const int r = w + NW * i;
-        if (r < Tv) {
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const int c = lane + WAVE * j;
-            if (c < dm) {
-              const float y = acc[i][j] + L.b_qkv[part * dm + c];
-              if (part == 1)
-                Kt[c * a.ldk + r] = y;
-              else
-                QV[r * a.ldq + (part == 2 ? dm : 0) + c] = y;
-            }
-          }
-        }
-      }
-    }
-    for (int e = tid; e < (Kr - Tv) * dm; e += NT)   // V rows past the valid keys: zero
-      QV[(Tv + e / dm) * a.ldq + dm + e % dm] = 0.f;
-    // ---- attention, one head at a time; O_h overwrites Q_h
-    for (int h = 0; h < a.H; ++h) {
-      __syncthreads();   // Q, K, V complete; P free
+  for (int li = 0; li < A.n_layers; ++li) {
+    const tav2_layer& L = A.layers[li];
+    f32x4 qv[DT];
+    if (li) __syncthreads();   // every wave is past its reads of K and V^T
+    if (live) {
+      // ---- Q in registers, K and V^T into LDS
+      load_vec<DT>(qv, L.b_qkv, dm);
+      phase(q, qv, x, layer_mat(L.W_qkv, 0, dm, dm, dm, 0), layer_mat(L.W_qkv, dm, dm, dm, dm, 0));
       {
-        float s[RI][1];
-        zero<RI, 1>(s);
-        gemm_lds<RI, 1>(s, QV + h * dh, a.ldq, Tv, dh, Kt + h * dh * a.ldk, a.ldk);
-        float x[RI], m[RI], p[RI], l[RI];
+        f32x4 k[DT];
+        load_vec<DT>(k, L.b_qkv + dm, dm);
+        phase(q, k, x, layer_mat(L.W_qkv, dm, dm, dm, dm, 0),
+              layer_mat(L.W_qkv, 2 * dm, dm, dm, dm, 0));
 #pragma unroll
-        for (int i = 0; i < RI; ++i) {
-          const int r = w + NW * i;
-          const bool ok = lane < Tv && (a.unmasked || lane <= r);
-          x[i] = ok ? s[i][0] * scale : -__builtin_inff();
-          m[i] = wave_max_f(x[i]);   // finite: key 0 is valid for every row
-        }
-#pragma unroll
-        for (int i = 0; i < RI; ++i) {
-          p[i] = x[i] == -__builtin_inff() ? 0.f : expf(x[i] - m[i]);
-          l[i] = wave_sum_f(p[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < RI; ++i) {
-          const int r = w + NW * i;
-          if (r < Tv && lane < Kr) P[r * a.ldp + lane] = p[i] / l[i];
-        }
+        for (int f = 0; f < DT; ++f)
+          *reinterpret_cast<f32x4*>(Ks + p * LDK + 16 * f + 4 * g) = k[f];
       }
-      __syncthreads();
       {
-        float o[RI][2];
-        zero<RI, 2>(o);
-        gemm_lds<RI, 2>(o, P, a.ldp, Tv, Kr, QV + dm + h * dh, a.ldq);
+        f32x4 v[DT];
+        load_vec<DT>(v, L.b_qkv + 2 * dm, dm);
+        phase(q, v, x, layer_mat(L.W_qkv, 2 * dm, dm, dm, dm, 0), layer_mat(L.W_o, 0, dm, dm, dm, 0));
 #pragma unroll
-        for (int i = 0; i < RI; ++i) {
-          const int r = w + NW * i;
-          if (r < Tv) {
+        for (int f = 0; f < DT; ++f)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              const int c = lane + WAVE * j;
-              if (c < dh) QV[r * a.ldq + h * dh + c] = o[i][j];
+          for (int i = 0; i < 4; ++i) Vt[(16 * f + 4 * g + i) * A.ldv + p] = v[f][i];
+      }
+    }
+    __syncthreads();
+    if (!live) continue;
+    // ---- attention, one head at a time: S^T = K Q^T (keys 16 t + 4 g + i of query c16)
+    f32x4 o[DT];
+#pragma unroll
+    for (int f = 0; f < DT; ++f) o[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nt = A.unmasked ? (Tv + 15) / 16 : w + 1;   // key tiles
+    const int lim = A.unmasked ? Tv : p + 1;              // keys the lane's query sees
+    for (int h = 0; h < A.H; ++h) {
+      const int h0 = h * dh, h1 = h0 + dh;   // heads begin and end at a multiple of 4
+      f32x4 s[MAX_NW];
+      float mx = -__builtin_inff();
+#pragma unroll
+      for (int t = 0; t < MAX_NW; ++t) {
+        s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (t < nt) {   // wave-uniform
+#pragma unroll
+          for (int f = 0; f < DT; ++f)
+            if (16 * f < h1 && 16 * f + 16 > h0) {   // uniform: the tile meets the head
+              const int k0 = 16 * f + 4 * g;
+              const bool in = k0 >= h0 && k0 < h1;
+              const f32x4 a = *reinterpret_cast<const f32x4*>(Ks + (16 * t + c16) * LDK + k0);
+#pragma unroll
+              for (int u = 0; u < 4; ++u) s[t] = mma(a[u], in ? qv[f][u] : 0.f, s[t]);
             }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            s[t][i] = 16 * t + 4 * g + i < lim ? s[t][i] * scale : -__builtin_inff();
+            mx = vmax(mx, s[t][i]);
           }
         }
       }
-    }
-    // ---- output projection + residual + LayerNorm 1
-    {
-      float acc[RI][2];
-      zero<RI, 2>(acc);
-      gemm_w<RI, 2>(acc, QV, a.ldq, Tv, dm, static_cast<const float*>(L.W_o), dm, dm, Ws, a.kc_shift);
-      add_norm<RI>(acc, X, a.ldx, Tv, dm, L.b_o, L.ln1_g, L.ln1_b);
-    }
-    // ---- FFN in hidden chunks of FC units + residual + LayerNorm 2
-    {
-      float acc2[RI][2];
-      zero<RI, 2>(acc2);
-      for (int c0 = 0; c0 < a.ffn; c0 += FC) {
-        const int nc = a.ffn - c0 < FC ? a.ffn - c0 : FC;
-        float acc1[RI][2];
-        zero<RI, 2>(acc1);
-        gemm_w<RI, 2>(acc1, X, a.ldx, Tv, dm, static_cast<const float*>(L.W_1) + int64_t(c0) * dm, dm,
-                      nc, Ws, a.kc_shift);
+      mx = xmax32(xmax16(mx));   // finite: key 0 is valid for every valid query
+      float l = 0.f;
 #pragma unroll
-        for (int i = 0; i < RI; ++i) {
-          const int r = w + NW * i;
-          if (r < Tv) {
+      for (int t = 0; t < MAX_NW; ++t)
+        if (t < nt) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              const int c = lane + WAVE * j;
-              if (c < nc) QV[r * a.ldh + c] = fmaxf(acc1[i][j] + L.b_1[c0 + c], 0.f);
-            }
+          for (int i = 0; i < 4; ++i) {
+            s[t][i] = s[t][i] == -__builtin_inff() ? 0.f : expf(s[t][i] - mx);
+            l += s[t][i];
           }
         }
-        gemm_w<RI, 2>(acc2, QV, a.ldh, Tv, nc, static_cast<const float*>(L.W_2) + c0, a.ffn, dm, Ws,
-                      a.kc_shift);
+      l = xsum32(xsum16(l));
+#pragma unroll
+      for (int f = 0; f < DT; ++f)
+        if (16 * f < h1 && 16 * f + 16 > h0) {
+          f32x4 oh = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int t = 0; t < MAX_NW; ++t)
+            if (t < nt) {
+              const f32x4 a = *reinterpret_cast<const f32x4*>(Vt + (16 * f + c16) * A.ldv + 16 * t + 4 * g);
+#pragma unroll
+              for (int u = 0; u < 4; ++u) oh = mma(a[u], s[t][u], oh);
+            }
+          const int k0 = 16 * f + 4 * g;
+          if (k0 >= h0 && k0 < h1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[f][i] = oh[i] / l;
+          }
+        }
+    }
+    // ---- x = LayerNorm 1(x + o W_o^T + b_o)
+    {
+      f32x4 b[DT], gn[DT];
+      load_vec<DT>(b, L.b_o, dm);
+      load_vec<DT>(gn, L.ln1_g, dm);
+#pragma unroll
+      for (int f = 0; f < DT; ++f) x[f] += b[f];
+      load_vec<DT>(b, L.ln1_b, dm);
+      phase(q, x, o, layer_mat(L.W_o, 0, dm, dm, dm, 0), layer_mat(L.W_1, 0, A.ffn, dm, dm, 0));
+      layer_norm<DT>(x, gn, b, dm);
+    }
+    // ---- x = LayerNorm 2(x + ReLU(x W_1^T + b_1) W_2^T + b_2), 16 DT hidden units at a time
+    {
+      f32x4 y[DT], gn[DT], b[DT];
+      load_vec<DT>(y, L.b_2, dm);
+      load_vec<DT>(gn, L.ln2_g, dm);
+      load_vec<DT>(b, L.ln2_b, dm);
+#pragma unroll
+      for (int f = 0; f < DT; ++f) y[f] += x[f];
+      for (int c0 = 0; c0 < A.ffn; c0 += DP) {
+        const int left = A.ffn - c0;
+        f32x4 hd[DT];
+        load_vec<DT>(hd, L.b_1 + c0, left);
+        const Mat w1 = layer_mat(L.W_1, c0, left, dm, dm, 0), w2 = layer_mat(L.W_2, 0, dm, left, A.ffn, c0);
+        phase(q, hd, x, w1, w2);
+#pragma unroll
+        for (int f = 0; f < DT; ++f)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) hd[f][i] = fmaxf(hd[f][i], 0.f);
+        phase(q, y, hd, w2,
+              left > DP ? layer_mat(L.W_1, c0 + DP, left - DP, dm, dm, 0)
+                        : li + 1 < A.n_layers ? layer_mat(A.layers[li + 1].W_qkv, 0, dm, dm, dm, 0)
+                                              : Mat{A.W_pool, dm, dm, dm});
       }
-      __syncthreads();   // every wave is past its reads of X's rows
-      add_norm<RI>(acc2, X, a.ldx, Tv, dm, L.b_2, L.ln2_g, L.ln2_b);
+      layer_norm<DT>(y, gn, b, dm);
+#pragma unroll
+      for (int f = 0; f < DT; ++f) x[f] = y[f];
     }
   }
 
   // ---- head: max over valid rows of X W_pool^T + b_pool; X of the last row
-  {
-    float acc[RI][2];
-    zero<RI, 2>(acc);
-    gemm_w<RI, 2>(acc, X, a.ldx, Tv, dm, a.W_pool, dm, dm, Ws, a.kc_shift);
+  if (live) {
+    const Mat wp{A.W_pool, dm, dm, dm};
+    f32x4 y[DT];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int c = lane + WAVE * j;
-      float mx = -__builtin_inff();
+    for (int f = 0; f < DT; ++f) y[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    phase<DT, PF, true>(q, y, x, wp, wp);
 #pragma unroll
-      for (int i = 0; i < RI; ++i)
-        if (w + NW * i < Tv) mx = fmaxf(mx, acc[i][j]);
-      if (c < dm) red[w * dm + c] = mx;
+    for (int f = 0; f < DT; ++f) {   // lane holds feature 16 f + c16 of tokens 4 g + i
+      float m = -__builtin_inff();
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (t0 + 4 * g + i < Tv) m = vmax(m, y[f][i]);
+      m = xmax32(xmax16(m));
+      if (g == 0) pool[w * DP + 16 * f + c16] = m;
     }
-    __syncthreads();
-    for (int c = tid; c < dm; c += NT) {
-      float mx = red[c];
+    if (p == Tv - 1) {
 #pragma unroll
-      for (int q = 1; q < NW; ++q) mx = fmaxf(mx, red[q * dm + c]);
-      out[c] = mx + a.b_pool[c];
-      out[dm + c] = X[(Tv - 1) * a.ldx + c];
+      for (int f = 0; f < DT; ++f)
+        if (16 * f + 4 * g < dm) *reinterpret_cast<f32x4*>(out + dm + 16 * f + 4 * g) = x[f];
     }
   }
+  __syncthreads();
+  const int nl = (Tv + TT - 1) / TT;   // waves with tokens
+  for (int c = tid; c < dm; c += blockDim.x) {
+    float m = pool[c];
+    for (int v = 1; v < nl; ++v) m = vmax(m, pool[v * DP + c]);
+    out[c] = m + A.b_pool[c];
+  }
+}
+
+// LDS floats of the LDS-staged form of this encoder, which sets the shapes accepted
+// (the kernel needs less; what it accepts is part of the interface).
+int shape_floats(int T, int d, int dm) {
+  constexpr int FC = 128, WS_LD = 132, NW = 4;
+  const int rows = round4(T), ldk = T % 2 ? T + 2 : T + 1;
+  int region = rows * (2 * dm + 4);
+  region = region > rows * (d + 4) ? region : rows * (d + 4);
+  region = region > rows * (FC + 4) ? region : rows * (FC + 4);
+  const int off = round4(rows * (dm + 4)) + round4(region) + round4(dm * ldk) +
+                  round4(rows * (round4(T) + 4)) + round4(dm) + round4(NW * dm) + 2 * F32_MAX_T;
+  return off + 16 * WS_LD;
 }
 
 }  // namespace f32e
@@ -494,11 +384,7 @@ bool encode_f32_fits(int T, const tav2_weights& w) {
   if (w.n_layers > f32e::MAX_LAYERS) return false;
   // every product's k and row strides in whole 16-byte groups
   if (w.d_model % 4 || (w.d_model / w.n_heads) % 4 || w.d_ffn % 4) return false;
-  f32e::Args a{};
-  a.d = w.d_in;
-  a.dm = w.d_model;
-  f32e::plan(a, T);
-  return a.lds_floats * 4 <= f32e::LDS_MAX;
+  return f32e::shape_floats(T, w.d_in, w.d_model) * 4 <= f32e::LDS_MAX;
 }
 
 hipError_t launch_encode_f32(const TokenSource& src, const void* cand_emb, int64_t total,
@@ -510,6 +396,7 @@ hipError_t launch_encode_f32(const TokenSource& src, const void* cand_emb, int64
   a.d = src.d;
   a.dm = w.d_model;
   a.H = w.n_heads;
+  a.dh = w.d_model / w.n_heads;
   a.ffn = w.d_ffn;
   a.n_layers = w.n_layers;
   a.W_in = static_cast<const float*>(w.W_in);
@@ -522,32 +409,25 @@ hipError_t launch_encode_f32(const TokenSource& src, const void* cand_emb, int64
   for (int i = 0; i < w.n_layers; ++i) a.layers[i] = w.layers[i];
   a.out = out;
   a.unmasked = unmasked ? 1 : 0;
-  f32e::plan(a, src.T);
-  const size_t lds = size_t(a.lds_floats) * 4;
-  // rows per wave: positions up to 16, 32, 48 or 64
-  const int ri = (src.T + 15) / 16 * 4;
-  const void* kernels[4] = {reinterpret_cast<const void*>(f32e::encode_f32_kernel<4>),
-                            reinterpret_cast<const void*>(f32e::encode_f32_kernel<8>),
-                            reinterpret_cast<const void*>(f32e::encode_f32_kernel<12>),
-                            reinterpret_cast<const void*>(f32e::encode_f32_kernel<16>)};
-  const int which = ri / 4 - 1;
-  static std::atomic<bool> done[64][4] = {};
+  const int nw = (src.T + f32e::TT - 1) / f32e::TT;
+  a.ldv = 16 * nw + 4;
+  const bool narrow = w.d_model <= 64;
+  const int dp = narrow ? 64 : 128;
+  const size_t lds = size_t(16 * nw * (dp + 4) + dp * a.ldv + nw * dp) * 4;
+  const size_t lds_max = size_t(64 * (128 + 4) + 128 * 68 + 4 * 128) * 4;
+  void (*const kernel)(f32e::Args) = narrow ? f32e::encode_f32_kernel<4, 4> : f32e::encode_f32_kernel<8, 2>;
+  static std::atomic<bool> done[64][2] = {};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64 || !done[dev][which].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(kernels[which], hipFuncAttributeMaxDynamicSharedMemorySize,
-                            f32e::LDS_MAX);
+  if (dev < 0 || dev >= 64 || !done[dev][narrow].load(std::memory_order_acquire)) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_max));
     if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < 64) done[dev][which].store(true, std::memory_order_release);
+    if (dev >= 0 && dev < 64) done[dev][narrow].store(true, std::memory_order_release);
   }
   ProfScope prof("encode_f32", st);
-  switch (which) {
-    case 0: f32e::encode_f32_kernel<4><<<unsigned(total), f32e::NT, lds, st>>>(a); break;
-    case 1: f32e::encode_f32_kernel<8><<<unsigned(total), f32e::NT, lds, st>>>(a); break;
-    case 2: f32e::encode_f32_kernel<12><<<unsigned(total), f32e::NT, lds, st>>>(a); break;
-    default: f32e::encode_f32_kernel<16><<<unsigned(total), f32e::NT, lds, st>>>(a); break;
-  }
+  hipLaunchKernelGGL(kernel, dim3(unsigned(total)), dim3(unsigned(nw * WAVE)), lds, st, a);
   return hipGetLastError();
 }
 

@@ -241,3 +241,18 @@ def test_packed_weights_equal_per_call_packing(k):
     b = run_path(inp, W, pack=True)
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("flags", [T.MASK_CAUSAL, T.MASK_NONE])
+@pytest.mark.parametrize("shape", [
+    # tiles of 16 tokens and features: one position; 16, 17, 33 and 49 positions; widths
+    # below, at and past a tile and past 64; heads that end inside a tile; FFN of one, 65
+    # and 130 units' worth of hidden tiles; d of one tile, of 64 + 16 and of 128 + 48
+    dict(d=16, d_model=4, n_heads=1, d_ffn=4, n_layers=1, k=1),
+    dict(d=80, d_model=20, n_heads=5, d_ffn=12, n_layers=2, k=16),
+    dict(d=16, d_model=60, n_heads=3, d_ffn=68, n_layers=1, k=17),
+    dict(d=176, d_model=68, n_heads=1, d_ffn=132, n_layers=1, k=33),
+    dict(d=48, d_model=100, n_heads=5, d_ffn=20, n_layers=2, k=49)])
+def test_fp32_encoder_tile_edges(shape, flags):
+    w = synth.scaled(synth.TINY, R=3, L=None, L_range=(1, 60), N=7, **shape)
+    check_workload(w, flags=flags)
