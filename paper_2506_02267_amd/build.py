@@ -16,7 +16,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtav2.so")
-SOURCES = ["api.cpp", "batcher.cpp", "profile.cpp", "select.hip", "select_fused.hip", "gather.hip",
+SOURCES = ["api.cpp", "batcher.cpp", "profile.cpp", "select.hip", "select_fused.hip",
+           "select_resident.hip", "gather.hip",
            "encoder_fused.hip", "encoder_fused_unmasked.hip", "encoder_small.hip",
            "encoder_f32.hip"]
 ARCH = "gfx950"
@@ -50,6 +51,8 @@ EXTRA_FLAGS = {"encoder_fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm",
                                      "-amdgpu-sched-strategy=max-ilp"],
                "select.hip": ["-fhip-fp32-correctly-rounded-divide-sqrt"],
+               "select_resident.hip": ["-fhip-fp32-correctly-rounded-divide-sqrt", "-mllvm",
+                                       "-amdgpu-mfma-vgpr-form"],
                "select_fused.hip": ["-fhip-fp32-correctly-rounded-divide-sqrt", "-mllvm",
                                     "-amdgpu-mfma-vgpr-form"]}
 

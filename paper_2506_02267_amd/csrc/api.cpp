@@ -135,6 +135,8 @@ size_t select_ws_bytes(const tav2_seq* s, const tav2_cands* c, int k) {
 // NN search writing rows of out_ld elements (the k results first).
 hipError_t run_select(const tav2_seq& s, const tav2_cands& c, int k, int32_t* out_idx,
                       float* out_score, int out_ld, int32_t* cand_req, void* ws, hipStream_t st) {
+  if (select_resident_applies(s, c))
+    return launch_select_resident(s, c, k, out_idx, out_score, out_ld, cand_req, st);
   if (select_fused_applies(s))
     return launch_select_fused(s, c, k, out_idx, out_score, out_ld, cand_req, ws, st);
   float* scores = static_cast<float*>(ws);

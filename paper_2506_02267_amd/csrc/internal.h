@@ -47,6 +47,12 @@ hipError_t launch_select_fused(const tav2_seq& seq, const tav2_cands& c, int k,
                                int32_t* out_idx, float* out_score, int out_ld, int32_t* cand_req,
                                void* ws, hipStream_t st);
 
+// ---- select_resident.hip: the same search in one kernel, every key in registers, for
+// narrow rows and few candidates
+bool select_resident_applies(const tav2_seq& seq, const tav2_cands& c);
+hipError_t launch_select_resident(const tav2_seq& seq, const tav2_cands& c, int k, int32_t* out_idx,
+                                  float* out_score, int out_ld, int32_t* cand_req, hipStream_t st);
+
 // ---- gather.hip
 // Where encoder tokens come from: either explicit token tensors, or the
 // selections into the request-level sources of Eq. 2: NN(S_LL, c), the kept

@@ -232,48 +232,65 @@ __device__ __forceinline__ void place_by_rank(const uint64_t* sel, int kk, int32
 // more than BIN_MOST values (many equal scores): the caller then selects another way.
 constexpr int NBINS = 1024;
 constexpr int BIN_MOST = 512;
-template <int NT, int PER, class Key, class Row>
-__device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, uint32_t kmin,
-                                              uint32_t kmax, int kk, uint32_t* hist, uint32_t* red,
-                                              uint64_t* sorted, int32_t* oi, float* os) {
+// Bins of one width over the keys kmin .. kmax, the largest keys first.
+struct KeyBins {
+  uint32_t kmax;
+  int shift;
+  __device__ __forceinline__ KeyBins(uint32_t kmin, uint32_t kmax_) : kmax(kmax_) {
+    const uint32_t range = kmax_ - kmin;
+    const int bits = range ? 32 - __builtin_clz(range) : 0;
+    shift = bits > 10 ? bits - 10 : 0;
+  }
+  __device__ __forceinline__ uint32_t operator()(uint32_t k) const { return (kmax - k) >> shift; }
+};
+// hist (complete: the caller has synchronised) becomes its exclusive prefix; returns
+// the bin that holds the need-th value (need >= 1) with `end` the values up to that
+// bin's end, or ~0 if there are fewer or that bin holds more than `most`.
+// red: NT / 64 + 2 words.  Ends with a barrier.
+template <int NT>
+__device__ __forceinline__ uint32_t find_bin(uint32_t* hist, uint32_t* red, uint32_t need, uint32_t most,
+                                             int& end) {
   constexpr int NW = NT / WAVE, BPT = NBINS / NT;   // bins per thread
-  static_assert(BPT == 4 || BPT == 2, "one vector of bins per thread");
-  typedef uint32_t bins_t __attribute__((ext_vector_type(BPT)));
   const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
-  const uint32_t range = kmax - kmin;
-  const int bits = range ? 32 - __builtin_clz(range) : 0, shift = bits > 10 ? bits - 10 : 0;
-  auto bin = [&](uint32_t k) { return (kmax - k) >> shift; };
-#pragma unroll
-  for (int e = 0; e < PER; ++e)
-    if (key(e)) atomicAdd(&hist[bin(key(e))], 1u);
-  __syncthreads();
-  // exclusive prefix over the bins, in place; the bin that holds the kk-th value
+  static_assert(BPT == 4 || BPT == 2 || BPT == 1, "one vector of bins per thread");
+  typedef uint32_t bins_t __attribute__((ext_vector_type(BPT)));
   const bins_t h = reinterpret_cast<const bins_t*>(hist)[tid];
   uint32_t sum = 0;
 #pragma unroll
   for (int i = 0; i < BPT; ++i) sum += h[i];
   const uint32_t incl = wave_incl_sum(sum);
   if (lane == WAVE - 1) red[wid] = incl;
-  if (tid == 0) red[NW + 1] = ~0u;   // (fewer than kk keys: nothing is placed)
+  if (tid == 0) red[NW + 1] = ~0u;
   __syncthreads();
   uint32_t at = incl - sum;
 #pragma unroll
   for (int w = 0; w < NW; ++w) at += w < wid ? red[w] : 0u;
-  const uint32_t need = uint32_t(kk);
   bins_t start;
 #pragma unroll
   for (int i = 0; i < BPT; ++i) {
     start[i] = at;
     if (at < need && need <= at + h[i]) {
-      red[NW] = at + h[i];                 // values up to that bin's end
-      red[NW + 1] = h[i] > uint32_t(BIN_MOST) ? ~0u : uint32_t(BPT * tid + i);
+      red[NW] = at + h[i];
+      red[NW + 1] = h[i] > most ? ~0u : uint32_t(BPT * tid + i);
     }
     at += h[i];
   }
   reinterpret_cast<bins_t*>(hist)[tid] = start;
   __syncthreads();
-  const int total = int(red[NW]);
-  const uint32_t last = red[NW + 1];
+  end = int(red[NW]);
+  return red[NW + 1];
+}
+template <int NT, int PER, class Key, class Row>
+__device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, uint32_t kmin,
+                                              uint32_t kmax, int kk, uint32_t* hist, uint32_t* red,
+                                              uint64_t* sorted, int32_t* oi, float* os) {
+  const KeyBins bin(kmin, kmax);
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (key(e)) atomicAdd(&hist[bin(key(e))], 1u);
+  __syncthreads();
+  int total;
+  const uint32_t last = find_bin<NT>(hist, red, uint32_t(kk), BIN_MOST, total);
   if (last == ~0u) return false;
 #pragma unroll
   for (int e = 0; e < PER; ++e)
@@ -282,7 +299,7 @@ __device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, ui
       if (b <= last) sorted[atomicAdd(&hist[b], 1u)] = sel_value(key(e), row(e));
     }
   __syncthreads();   // hist[b] is now the end of bin b <= last, and the start of the next
-  for (int i = tid; i < total; i += NT) {
+  for (int i = threadIdx.x; i < total; i += NT) {
     const uint64_t me = sorted[i];
     const uint32_t b = bin(sel_key(me));
     const int s0 = b ? int(hist[b - 1]) : 0, s1 = int(hist[b]);

@@ -1,0 +1,321 @@
+// NN search of Eq. 3 for narrow rows and few candidates in one kernel: a workgroup
+// scores every row of the request for one candidate and keeps the products in registers,
+// so there is no sample, no threshold, no survivor list in memory and no fallback launch.
+//
+// A thread loads whole rows (row NT j + thread).  Products: 32x32x16 MFMAs with the
+// candidate in every row of the A operand; the lower lanes' rows are one tile of 32, the
+// upper lanes' the other.  The operands and the k order are the other search kernels',
+// and so are the scores' bits.
+//
+// Selection: every thread's rows fall into four groups, the groups' largest estimates
+// are binned, and the bin that holds the k-th largest of them bounds the k-th key from
+// below, closely (k = 256 of 16384 rows: about 300 rows reach it).  The rows that reach
+// it get their exact score and are placed by bins.  Where a bin or the list overflows
+// (many equal scores), the k-th key is found bit by bit.
+//
+// What bounds it: launch, first loads and selection are about 10 us; each 1024 rows add
+// 0.5 to 1 us: every workgroup reads all rows from L2 and turns codes into bf16.
+#include <type_traits>
+
+#include "common.h"
+#include "internal.h"
+#include "select_common.h"
+
+namespace tav2 {
+namespace sr {
+
+struct Args {
+  const void* emb;
+  const int64_t* seq_off;
+  const int32_t* seq_len;
+  const bf16_t* cand;
+  const int64_t* cand_off;
+  int d, max_len, k, out_ld;
+  int32_t* out_idx;
+  float* out_score;
+  int32_t* cand_req;
+};
+constexpr int NT = 1024;
+constexpr int GROUPS = 4;    // groups of a thread's rows
+constexpr int LIST = 2048;   // rows that may be among the k best, at most
+static_assert(NBINS == NT && GROUPS * NT >= TAV2_K_MAX, "one bin per thread; enough groups");
+
+// Eight codes as bf16: at most 8 significant bits, so the upper half of the float is exact.
+__device__ __forceinline__ bf16x8 codes(uint32_t x, uint32_t y) {
+  uint32_t p[4];
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    const uint32_t w = j < 4 ? x : y;
+    const uint32_t a = __float_as_uint(float(int8_t((w >> (8 * (j & 3))) & 0xFF)));
+    const uint32_t b = __float_as_uint(float(int8_t((w >> (8 * (j & 3) + 8)) & 0xFF)));
+    p[j / 2] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+  }
+  return as_bf16x8(make_uint4(p[0], p[1], p[2], p[3]));
+}
+
+// The kk best of the workgroup's keys (key[j]: row j NT + thread, 0: none), found bit by
+// bit: every key above the kk-th, then the lowest rows equal to it.  sel: kk values.
+template <int NT, int RPT>
+__device__ __noinline__ void place_by_bits(const uint32_t* key, int kk, uint32_t* red, uint64_t* sel,
+                                           int32_t* oi, float* os) {
+  constexpr int NW = NT / WAVE;
+  const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
+  auto total = [&](int c) {   // over the workgroup, of a wave-uniform count
+    __syncthreads();
+    if (lane == 0) red[wid] = uint32_t(c);
+    __syncthreads();
+    int t = 0;
+    for (int w = 0; w < NW; ++w) t += int(red[w]);
+    return t;
+  };
+  uint32_t t = 0;
+  for (int b = 31; b >= 0; --b) {
+    const uint32_t probe = t | (1u << b);
+    int c = 0;
+    for (int j = 0; j < RPT; ++j) c += __popcll(__builtin_amdgcn_ballot_w64(key[j] >= probe));
+    if (total(c) >= kk) t = probe;
+  }
+  int above = 0;   // keys above t, in any order; then those equal to it, in row order
+  for (int pass = 0; pass < 2; ++pass)
+    for (int j = 0; j < RPT; ++j) {
+      const bool in = pass ? key[j] == t : key[j] > t;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+      __syncthreads();
+      if (lane == 0) red[wid] = uint32_t(__popcll(m));
+      __syncthreads();
+      int before = above, all = 0;
+      for (int w = 0; w < NW; ++w) {
+        before += w < wid ? int(red[w]) : 0;
+        all += int(red[w]);
+      }
+      const int pos = before + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0)));
+      if (in && pos < kk) sel[pos] = sel_value(key[j], j * NT + tid);
+      above += all;
+    }
+  __syncthreads();
+  place_by_rank<NT>(sel, kk, oi, os);
+}
+
+// A row's score from its product (and, for codes, its sum of squares): exact, and the
+// estimate through the hardware reciprocal square root.  The two have the same sign and
+// keys at most SLACK apart (relative error below 2^-21); a product that is not a number
+// is its own score in both.
+constexpr uint32_t SLACK = 64;
+template <bool I8>
+__device__ __forceinline__ uint32_t exact_key(float dot, float ss) {
+  return score_key(I8 && dot == dot ? i8_score(dot, ss) : dot);
+}
+template <bool I8>
+__device__ __forceinline__ uint32_t estimate_key(float dot, float ss) {
+  const float est = ss > 0.f ? dot * __builtin_amdgcn_rsqf(ss) : 0.f;
+  return score_key(I8 && dot == dot ? est : dot);
+}
+
+// NT threads, RPT rows per thread (the rows fit NT x RPT), d = 16 KB.
+template <bool I8, int KB, int RPT>
+__global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
+  __shared__ __attribute__((aligned(16))) uint64_t sorted[TAV2_K_MAX + BIN_MOST];
+  __shared__ float list_dot[LIST], list_ss[LIST];
+  __shared__ uint16_t list_row[LIST];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[NBINS];
+  __shared__ uint32_t red[2 * NT / WAVE + 2];
+  __shared__ uint32_t listed;
+  const int r = blockIdx.y;
+  const int64_t n = A.cand_off[r] + int64_t(blockIdx.x);
+  if (n >= A.cand_off[r + 1]) return;
+  const int tid = threadIdx.x, lane = tid % WAVE, hf = lane / 32;
+  if (A.cand_req && tid == 0) A.cand_req[n] = r;   // the candidate's request, for the encoder
+  const int L = min(A.seq_len[r], A.max_len);
+  const int k = A.k, kk = k < L ? k : L;
+  int32_t* oi = A.out_idx + n * A.out_ld;
+  float* os = A.out_score + n * A.out_ld;
+  for (int p = kk + tid; p < k; p += NT) {
+    oi[p] = -1;
+    os[p] = -__builtin_inff();
+  }
+  if (kk == 0) return;
+  constexpr int d = 16 * KB;
+  bf16x8 cf[KB];   // the candidate, in every row of the A operand
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+    cf[kb] = as_bf16x8(*reinterpret_cast<const uint4*>(A.cand + n * d + 16 * kb + 8 * hf));
+  constexpr int ROW = I8 ? d : 2 * d;   // bytes
+  constexpr int AHEAD = RPT < 16 ? 128 / ROW : 2;   // (16 rows: 128 registers)
+  const uint8_t* emb = static_cast<const uint8_t*>(A.emb) + A.seq_off[r] * ROW;
+  uint4 raw[AHEAD][ROW / 16];   // the lane's row NT j + tid, j modulo AHEAD
+  auto load = [&](int j) {
+    const uint8_t* p = emb + min(NT * j + tid, L - 1) * ROW;   // clamped; not kept
+#pragma unroll
+    for (int i = 0; i < ROW / 16; ++i) raw[j % AHEAD][i] = reinterpret_cast<const uint4*>(p)[i];
+  };
+#pragma unroll
+  for (int j = 0; j < AHEAD; ++j) load(j);
+  hist[tid] = 0u;
+  if (tid == 0) listed = 0u;
+  float dot[RPT], ss[RPT];   // of row NT j + thread
+  uint32_t gm[GROUPS] = {};   // the largest estimates of rows j modulo GROUPS
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    ss[j] = 0.f;
+    f32x16 acc[2] = {f32x16{}, f32x16{}};
+    uint32_t x[ROW / 4];
+#pragma unroll
+    for (int i = 0; i < ROW / 16; ++i) {
+      const uint4 q = raw[j % AHEAD][i];
+      x[4 * i] = q.x;
+      x[4 * i + 1] = q.y;
+      x[4 * i + 2] = q.z;
+      x[4 * i + 3] = q.w;
+    }
+    if (j + AHEAD < RPT) load(j + AHEAD);
+    if constexpr (I8) {
+      int sq = 0;
+#pragma unroll
+      for (int i = 0; i < ROW / 4; ++i) sq = __builtin_amdgcn_sdot4(int(x[i]), int(x[i]), sq, false);
+      ss[j] = float(sq);
+    }
+    // the lower lanes hold tile 0's rows, the upper tile 1's: words of k and k + 8
+    // change places across the halves and become the two tiles' operands
+    constexpr int H = I8 ? 2 : 4;   // words of 8 k
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      uint32_t t0[4], t1[4];
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        const auto y = __builtin_amdgcn_permlane32_swap(x[2 * H * kb + i], x[2 * H * kb + H + i], false, false);
+        t0[i] = y[0];
+        t1[i] = y[1];
+      }
+      if constexpr (I8) {
+        acc[0] = mfma32(cf[kb], codes(t0[0], t0[1]), acc[0]);
+        acc[1] = mfma32(cf[kb], codes(t1[0], t1[1]), acc[1]);
+      } else {
+        acc[0] = mfma32(cf[kb], as_bf16x8(make_uint4(t0[0], t0[1], t0[2], t0[3])), acc[0]);
+        acc[1] = mfma32(cf[kb], as_bf16x8(make_uint4(t1[0], t1[1], t1[2], t1[3])), acc[1]);
+      }
+    }
+    dot[j] = hf ? acc[1][0] : acc[0][0];
+    gm[j % GROUPS] = max(gm[j % GROUPS], NT * j + tid < L ? estimate_key<I8>(dot[j], ss[j]) : 0u);
+  }
+  uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+  for (int q = 0; q < GROUPS; ++q)
+    if (gm[q]) {
+      lo = min(lo, gm[q]);
+      hi = max(hi, gm[q]);
+    }
+  block_min_max<NT>(lo, hi, red);
+  const KeyBins gbin(lo, hi);
+#pragma unroll
+  for (int q = 0; q < GROUPS; ++q)
+    if (gm[q]) atomicAdd(&hist[gbin(gm[q])], 1u);
+  __syncthreads();
+  int end;
+  const uint32_t last = find_bin<NT>(hist, red, uint32_t(kk), ~0u, end);
+  // kk estimates reach the smallest key of that bin (min(L, GROUPS x NT) >= kk groups
+  // have a row), so the kk-th exact key is at most SLACK below it, and the estimates of
+  // the kk best rows 2 SLACK
+  const uint64_t span = ((uint64_t(last) + 1) << gbin.shift) + 2 * SLACK;
+  const uint32_t least = span >= uint64_t(hi) ? 1u : hi - uint32_t(span) + 1u;
+  hist[tid] = 0u;
+  // the rows whose estimate reaches it
+  uint32_t m = 0;
+#pragma unroll
+  for (int j = 0; j < RPT; ++j)
+    m |= uint32_t(NT * j + tid < L && estimate_key<I8>(dot[j], ss[j]) >= least) << j;
+  const uint32_t mine = uint32_t(__popc(m)), incl = wave_incl_sum(mine);
+  uint32_t at = 0;
+  if (lane == WAVE - 1) at = atomicAdd(&listed, incl);
+  at = uint32_t(__builtin_amdgcn_readlane(int(at), WAVE - 1)) + incl - mine;
+#pragma unroll
+  for (int j = 0; j < RPT; ++j)
+    if ((m >> j) & 1u) {
+      if (at < uint32_t(LIST)) {
+        list_dot[at] = dot[j];
+        list_ss[at] = ss[j];
+        list_row[at] = uint16_t(NT * j + tid);
+      }
+      ++at;
+    }
+  __syncthreads();
+  const uint32_t total = listed;
+  bool placed = false;
+  if (total <= uint32_t(LIST)) {
+    uint32_t key[LIST / NT];
+    int row[LIST / NT];
+#pragma unroll
+    for (int e = 0; e < LIST / NT; ++e) {
+      const uint32_t i = uint32_t(NT * e + tid);
+      key[e] = 0u;
+      row[e] = 0;
+      if (i < total) {
+        key[e] = exact_key<I8>(list_dot[i], list_ss[i]);
+        row[e] = list_row[i];
+      }
+    }
+    const uint32_t kmin = least > SLACK ? least - SLACK : 1u;
+    const uint32_t kmax = hi < ~0u - SLACK ? hi + SLACK : ~0u;
+    placed = place_by_bins<NT, LIST / NT>([&](int e) { return key[e]; }, [&](int e) { return row[e]; },
+                                          kmin, kmax, kk, hist, red, sorted, oi, os);
+  }
+  if (!placed) {
+    uint32_t key[RPT];
+#pragma unroll
+    for (int j = 0; j < RPT; ++j)
+      key[j] = NT * j + tid < L ? max(exact_key<I8>(dot[j], ss[j]), 1u) : 0u;
+    place_by_bits<NT, RPT>(key, kk, red, sorted, oi, os);
+  }
+}
+
+}  // namespace sr
+
+// One workgroup per CU, or two where the registers of two fit (up to 4 rows a thread).
+// us, this kernel : the launches it takes the place of; k 128, k 1000 at 8192 rows:
+//   candidates, d   rows 2000     4000        8192        16384
+//   256, 32 int8    11.4 : 15.3   11.6 : 20.3 15.5 : 44.0 25.1 : 29.0
+//   256, 32 bf16    11.1 : 13.6   11.1 : 18.6 15.5 : 50.2 (24.0 : 24.8)
+//   256, 64 int8    14.2 : 14.7   14.5 : 17.5 22.4 : 44.2 (39.8 : 30.1)
+//   500, 32 int8    13.4 : 16.6   17.9 : 21.8 (28.9 : 46.8) (47.5 : 33.7)
+//   500, 32 bf16    13.1 : 15.4   14.7 : 20.8
+//   256, 64 bf16    (13.2 : 14.7  21.3 : 17.5 42.8 : 52.1 71.2 : 27.2)
+// Those in brackets are not taken: rows above 64 bytes, more than 512 KB a request.
+bool select_resident_applies(const tav2_seq& s, const tav2_cands& c) {
+  if (s.dtype != TAV2_BF16 && s.dtype != TAV2_I8) return false;
+  if (s.d != 32 && s.d != 64) return false;
+  const int row = s.dtype == TAV2_I8 ? s.d : 2 * s.d;   // bytes
+  if (row > 64 || int64_t(s.max_len) * row > 512 * 1024) return false;
+  return c.total <= 256 || (c.total <= 512 && s.d == 32 && s.max_len <= 4 * sr::NT);
+}
+
+hipError_t launch_select_resident(const tav2_seq& seq, const tav2_cands& c, int k, int32_t* out_idx,
+                                  float* out_score, int out_ld, int32_t* cand_req, hipStream_t st) {
+  if (seq.num_requests == 0 || c.total == 0) return hipSuccess;
+  sr::Args A{};
+  A.emb = seq.emb;
+  A.seq_off = seq.offset;
+  A.seq_len = seq.len;
+  A.cand = static_cast<const bf16_t*>(c.emb);
+  A.cand_off = c.offset;
+  A.d = seq.d;
+  A.max_len = seq.max_len;
+  A.k = k;
+  A.out_ld = out_ld;
+  A.out_idx = out_idx;
+  A.out_score = out_score;
+  A.cand_req = cand_req;
+  const bool i8 = seq.dtype == TAV2_I8;
+  const dim3 grid(unsigned(c.max_count), unsigned(seq.num_requests));
+  ProfScope prof("nn_resident", st);
+#define SR_LAUNCH(I8, KB)                                                                        \
+  (seq.max_len <= 2 * sr::NT   ? sr::select_resident_kernel<I8, KB, 2><<<grid, sr::NT, 0, st>>>(A) \
+   : seq.max_len <= 4 * sr::NT ? sr::select_resident_kernel<I8, KB, 4><<<grid, sr::NT, 0, st>>>(A) \
+                               : sr::select_resident_kernel<I8, KB, 8><<<grid, sr::NT, 0, st>>>(A))
+  if (!i8) SR_LAUNCH(false, 2);
+  else if (seq.d == 64) SR_LAUNCH(true, 4);
+  else if (seq.max_len <= 8 * sr::NT) SR_LAUNCH(true, 2);
+  else sr::select_resident_kernel<true, 2, 16><<<grid, sr::NT, 0, st>>>(A);
+#undef SR_LAUNCH
+  return hipGetLastError();
+}
+
+}  // namespace tav2

@@ -248,3 +248,27 @@ def test_long_row_bins_with_equal_scores(dtype, copies, k):
     torch.cuda.synchronize()
     ref_i, ref_s = oracle_select(inp, k)
     assert_select_equal(idx, score, ref_i, ref_s)
+
+
+@pytest.mark.parametrize("dtype,d", [("i8", 32), ("bf16", 32), ("i8", 64)])
+@pytest.mark.parametrize("L,k", [(1, 4), (1023, 1024), (2049, 700), (4096, 1024), (8192, 33),
+                                 (16384, 256)])
+@pytest.mark.parametrize("ties", ["none", "some", "all"])
+def test_resident_rows(dtype, d, L, k, ties):
+    """The search with every product in registers: the edges of its rows per thread, fewer
+    rows than places, a ragged second request, equal scores past the bins' limit."""
+    print(f"resident {dtype} d={d} L={L} k={k} {ties}", flush=True)
+    base = synth.SELECT_I8 if dtype == "i8" else synth.SINGLE
+    w = synth.scaled(base, R=3, L=L, N=4, k=k, d=d, tie_frac=0.0)
+    inp = synth.make_inputs(w, seed=L + d)
+    inp.seq.length[1:] = [L // 3, 0]
+    if ties != "none":
+        n = min(L, 900) if ties == "some" else L
+        rows = np.random.default_rng(L).permutation(L)[:n]
+        best = int(np.argmax(inp.seq.emb[:L].astype(np.float64) @ inp.cand[0]))
+        inp.seq.emb[rows] = inp.seq.emb[best]
+    seq, _, cands = upload(inp)
+    idx, score = T.nn_select(seq, cands, k)
+    torch.cuda.synchronize()
+    ref_i, ref_s = oracle_select(inp, k)
+    assert_select_equal(idx, score, ref_i, ref_s)
