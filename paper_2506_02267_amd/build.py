@@ -18,8 +18,8 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtav2.so")
 SOURCES = ["api.cpp", "batcher.cpp", "profile.cpp", "select.hip", "select_fused.hip",
            "select_resident.hip", "gather.hip",
-           "encoder_fused.hip", "encoder_fused_unmasked.hip", "encoder_small.hip",
-           "encoder_f32.hip"]
+           "encoder_fused.hip", "encoder_fused_unmasked.hip", "encoder_fused_short.hip",
+           "encoder_small.hip", "encoder_f32.hip"]
 ARCH = "gfx950"
 
 
@@ -47,6 +47,7 @@ def compile_flags():
 # must round correctly (the compiler's default for HIP, stated explicitly).
 EXTRA_FLAGS = {"encoder_fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_fused_unmasked.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "encoder_fused_short.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "encoder_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm",
                                      "-amdgpu-sched-strategy=max-ilp"],

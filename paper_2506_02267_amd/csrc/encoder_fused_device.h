@@ -284,33 +284,33 @@ struct NoSide {
 
 // acc[ft][tt] += C^T: features 64 w + 32 ft (packed rows of cur), tokens 32 tt
 // (rows of ACT in LDS, columns 16 j), over Cur::NKB k-blocks.
-template <class Cur, class Nxt, class Side = NoSide>
-__device__ __forceinline__ void resid_phase(f32x16 (&acc)[2][4], Pre& pre, const WSeg& cur,
+template <class Cur, class Nxt, class Side = NoSide, int TT>
+__device__ __forceinline__ void resid_phase(f32x16 (&acc)[2][TT], Pre& pre, const WSeg& cur,
                                             const WSeg& nxt, const bf16_t* ACT, int ald,
                                             Side&& side = Side{}) {
   static_assert(Cur::NR == 2, "residual phases have two row tiles per wave");
   FZ_LANE_VARS
   constexpr int NKB = Cur::NKB;
   bf16x8 wq[NKB][2];
-  bf16x8 xq[NKB][4];
+  bf16x8 xq[NKB][TT];
   const bf16_t* arow = ACT + l32 * ald + 8 * hf;
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt) xq[0][tt] = lfrag(arow + 32 * tt * ald);
+  for (int tt = 0; tt < TT; ++tt) xq[0][tt] = lfrag(arow + 32 * tt * ald);
 #pragma unroll
   for (int j = 0; j < NKB; ++j) {
     if (j + 1 < Cur::NX) {
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) xq[j + 1][tt] = lfrag(arow + 32 * tt * ald + (j + 1) * 16);
+      for (int tt = 0; tt < TT; ++tt) xq[j + 1][tt] = lfrag(arow + 32 * tt * ald + (j + 1) * 16);
     } else if (j + 1 < NKB) {   // the bias k-block
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) xq[j + 1][tt] = bias_ones();
+      for (int tt = 0; tt < TT; ++tt) xq[j + 1][tt] = bias_ones();
     }
     // token tile by token tile: each tile's operand is last read two products into
     // the k-block rather than six, which leaves the register allocator more room
     {
       const bf16x8 a0 = stream_frag<Cur>(wq, pre, j, 0), a1 = stream_frag<Cur>(wq, pre, j, 1);
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
+      for (int tt = 0; tt < TT; ++tt) {
         acc[0][tt] = mfma32(a0, xq[j][tt], acc[0][tt]);
         acc[1][tt] = mfma32(a1, xq[j][tt], acc[1][tt]);
       }
@@ -339,29 +339,29 @@ __device__ __forceinline__ bf16x8 onehot8(int idx) {   // 1.0 at element idx (no
 
 // acc += E_act[act_t] + E_time[time_t] for the block's tokens: k-block 0 holds the
 // 8 action types, k-blocks 1..4 the 64 time buckets (at columns 16 + bucket).
-template <class Nxt>
-__device__ __forceinline__ void table_phase(f32x16 (&acc)[2][4], Pre& pre, const WSeg& cur,
+template <class Nxt, int TT>
+__device__ __forceinline__ void table_phase(f32x16 (&acc)[2][TT], Pre& pre, const WSeg& cur,
                                             const WSeg& nxt, const int* tinfo) {
   FZ_LANE_VARS
   constexpr int NKB = ShTab::NKB;
   bf16x8 wq[NKB][2];
-  int ka[4], kt[4];   // the token's one-hot column, relative to this lane's k-rows
+  int ka[TT], kt[TT];   // the token's one-hot column, relative to this lane's k-rows
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt) {
+  for (int tt = 0; tt < TT; ++tt) {
     const int info = tinfo[tt * 32 + l32];
     ka[tt] = (info & 0xFF) - 8 * hf;
     kt[tt] = 16 + ((info >> 8) & 0xFF) - 8 * hf;
   }
 #pragma unroll
   for (int j = 0; j < NKB; ++j) {
-    bf16x8 b[4];
+    bf16x8 b[TT];
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) b[tt] = onehot8(j == 0 ? ka[tt] : kt[tt] - 16 * j);
+    for (int tt = 0; tt < TT; ++tt) b[tt] = onehot8(j == 0 ? ka[tt] : kt[tt] - 16 * j);
 #pragma unroll
     for (int ft = 0; ft < 2; ++ft) {
       const bf16x8 a = stream_frag<ShTab>(wq, pre, j, ft);
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) acc[ft][tt] = mfma32(a, b[tt], acc[ft][tt]);
+      for (int tt = 0; tt < TT; ++tt) acc[ft][tt] = mfma32(a, b[tt], acc[ft][tt]);
     }
     stream_fetch<ShTab, Nxt>(wq, pre, cur, nxt, j, lane);
     sched_fence();
@@ -370,8 +370,8 @@ __device__ __forceinline__ void table_phase(f32x16 (&acc)[2][4], Pre& pre, const
 
 // acc += E_pos[p0 + r] for the block's tokens r: the block's 128 positions are
 // the 8 k-blocks of E_pos^T from position p0; k-block j only meets token tile j / 2.
-template <class Nxt>
-__device__ __forceinline__ void pos_phase(f32x16 (&acc)[2][4], Pre& pre, const WSeg& cur,
+template <class Nxt, int TT>
+__device__ __forceinline__ void pos_phase(f32x16 (&acc)[2][TT], Pre& pre, const WSeg& cur,
                                           const WSeg& nxt) {
   FZ_LANE_VARS
   constexpr int NKB = ShPos::NKB;
@@ -382,7 +382,7 @@ __device__ __forceinline__ void pos_phase(f32x16 (&acc)[2][4], Pre& pre, const W
     const bf16x8 b = onehot8(l32 - 16 * (j & 1) - 8 * hf);
 #pragma unroll
     for (int ft = 0; ft < 2; ++ft)
-      acc[ft][tt] = mfma32(stream_frag<ShPos>(wq, pre, j, ft), b, acc[ft][tt]);
+      if (tt < TT) acc[ft][tt % TT] = mfma32(stream_frag<ShPos>(wq, pre, j, ft), b, acc[ft][tt % TT]);
     stream_fetch<ShPos, Nxt>(wq, pre, cur, nxt, j, lane);
     sched_fence();
   }
@@ -414,32 +414,33 @@ __device__ __forceinline__ void ln_params_store(const LnParams& q, float* P) {
 // with P = [g | b] in LDS; Xs <- bf16(x).  Each wave holds 64
 // features of every token: per-token partial sums meet in LDS (red: [BT][4] sums,
 // then [BT][4] sums of squares).  Ends with a barrier.
-__device__ __forceinline__ void layer_norm(f32x16 (&acc)[2][4], const float* P, float* red,
+template <int TT>
+__device__ __forceinline__ void layer_norm(f32x16 (&acc)[2][TT], const float* P, float* red,
                                            bf16_t* Xs) {
   FZ_LANE_VARS
-  float s[4] = {0.f, 0.f, 0.f, 0.f}, ss[4] = {0.f, 0.f, 0.f, 0.f};
+  float s[TT] = {}, ss[TT] = {};
 #pragma unroll
   for (int ft = 0; ft < 2; ++ft)
 #pragma unroll
     for (int r = 0; r < 16; ++r)
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
+      for (int tt = 0; tt < TT; ++tt) {
         const float v = acc[ft][tt][r];
         s[tt] += v;
         ss[tt] = fmaf(v, v, ss[tt]);
       }
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt) {   // both lane halves end with the full sums
+  for (int tt = 0; tt < TT; ++tt) {   // both lane halves end with the full sums
     s[tt] = xsum32(s[tt]);
     ss[tt] = xsum32(ss[tt]);
   }
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt)     // half 0 stores the sums, half 1 the squares
+  for (int tt = 0; tt < TT; ++tt)     // half 0 stores the sums, half 1 the squares
     red[hf * BT * 4 + (tt * 32 + l32) * 4 + w] = hf ? ss[tt] : s[tt];
   __syncthreads();
-  float rstd[4], shift[4];   // x_hat = x rstd + shift
+  float rstd[TT], shift[TT];   // x_hat = x rstd + shift
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt) {
+  for (int tt = 0; tt < TT; ++tt) {
     const int tok = tt * 32 + l32;
     const float4 a = *reinterpret_cast<const float4*>(red + tok * 4);
     const float4 b = *reinterpret_cast<const float4*>(red + BT * 4 + tok * 4);
@@ -456,7 +457,7 @@ __device__ __forceinline__ void layer_norm(f32x16 (&acc)[2][4], const float* P, 
       const float4 gg = *reinterpret_cast<const float4*>(P + f);
       const float4 bb = *reinterpret_cast<const float4*>(P + DM + f);
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
+      for (int tt = 0; tt < TT; ++tt) {
         const float v0 = fmaf(fmaf(acc[ft][tt][4 * j], rstd[tt], shift[tt]), gg.x, bb.x);
         const float v1 = fmaf(fmaf(acc[ft][tt][4 * j + 1], rstd[tt], shift[tt]), gg.y, bb.y);
         const float v2 = fmaf(fmaf(acc[ft][tt][4 * j + 2], rstd[tt], shift[tt]), gg.z, bb.z);
@@ -494,7 +495,8 @@ __device__ __forceinline__ int pool_feature() {
                 ((l32 & 16) >> 4);
   return 64 * w + (k >> 4) * 32 + 8 * ((k & 15) >> 2) + 4 * hf + (k & 3);
 }
-__device__ __forceinline__ float pool_block(f32x16 (&acc)[2][4], float pm, int nvalid) {
+template <int TT>
+__device__ __forceinline__ float pool_block(f32x16 (&acc)[2][TT], float pm, int nvalid) {
   FZ_LANE_VARS
   float v[32];
 #pragma unroll
@@ -503,7 +505,7 @@ __device__ __forceinline__ float pool_block(f32x16 (&acc)[2][4], float pm, int n
     for (int r = 0; r < 16; ++r) {
       float m = -__builtin_inff();
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt)
+      for (int tt = 0; tt < TT; ++tt)
         if (tt * 32 + l32 < nvalid) m = vmax(m, acc[ft][tt][r]);
       v[ft * 16 + r] = m;
     }
@@ -692,13 +694,13 @@ __device__ __forceinline__ void attn_segment2(AttnState<DH>& sa, AttnState<DH>& 
   attn_segment1<DH, DQA, NPA, FIRST>(sa, Kl, kld, Vl, vld, col0, lane, kvl);
   attn_segment1<DH, DQB, NPB, FIRST>(sb, Kl, kld, Vl, vld, col0, lane, kvl);
 }
-// The block's own keys for wave W: tiles W and 7 - W see W / 2 + 1 and
-// (7 - W) / 2 + 1 pairs.
-template <int DH, int W>
+// The block's own keys for wave W: of NQ query tiles, tiles W and NQ - 1 - W see
+// W / 2 + 1 and (NQ - 1 - W) / 2 + 1 pairs.
+template <int DH, int NQ, int W>
 __device__ __forceinline__ void attn_own(AttnState<DH>& sa, AttnState<DH>& sb, const bf16_t* Ks,
                                          const bf16_t* Vts, int col0, int lane) {
-  attn_segment2<DH, W, 7 - W, W / 2 + 1, (7 - W) / 2 + 1, true>(sa, sb, Ks, QLD, Vts, VLD, col0,
-                                                                lane);
+  attn_segment2<DH, W, NQ - 1 - W, W / 2 + 1, (NQ - 1 - W) / 2 + 1, true>(sa, sb, Ks, QLD, Vts, VLD,
+                                                                          col0, lane);
 }
 
 // O = O^T / l into the tile's rows of Qs (the tile's Q is already in registers).
@@ -712,6 +714,18 @@ __device__ __forceinline__ void attn_finish(AttnState<DH>& st, bf16_t* Qs, int c
   for (int dt = 0; dt < DH / 16; ++dt)
     st4(Qs + (16 * qt + c16) * QLD + col0 + 16 * dt + 4 * gq, st.o[dt][0] * inv, st.o[dt][1] * inv,
         st.o[dt][2] * inv, st.o[dt][3] * inv);
+}
+
+// A block without earlier keys: the wave's two tiles from Q to O.
+template <int DH, int NQ, int W>
+__device__ __forceinline__ void attn_short(bf16_t* Qs, const bf16_t* Ks, const bf16_t* Vts, int col0,
+                                           int lane) {
+  AttnState<DH> sa, sb;
+  attn_init<DH>(sa, Qs, col0, W);
+  attn_init<DH>(sb, Qs, col0, NQ - 1 - W);
+  attn_own<DH, NQ, W>(sa, sb, Ks, Vts, col0, lane);
+  attn_finish<DH>(sa, Qs, col0, W);
+  attn_finish<DH>(sb, Qs, col0, NQ - 1 - W);
 }
 
 // Cached keys [c0, c0 + 128) of head group g (K rows and V^T columns): the loads
@@ -758,7 +772,7 @@ __device__ __forceinline__ void cache_put(const CacheChunk& ch, bf16_t* Kc, bf16
 // look-ahead, after the own keys (issued earlier, its registers would be copied
 // around the wave-specific code, and the copies would wait for the loads).
 // NM: the unmasked mode (a single block: every query sees every valid key).
-template <int DH, bool NM, class Prime>
+template <int DH, bool NM, int TT, class Prime>
 __device__ __forceinline__ void attend_group(int g, int p0, bf16_t* Qs, const bf16_t* Ks,
                                              const bf16_t* Vts, const bf16_t* kc,
                                              const bf16_t* vc, int tpad, bf16_t* Kc, bf16_t* Vc,
@@ -766,7 +780,21 @@ __device__ __forceinline__ void attend_group(int g, int p0, bf16_t* Qs, const bf
   constexpr int NH = 64 / DH;
   const int lane = otid() % WAVE;
   const int w = __builtin_amdgcn_readfirstlane(otid() / WAVE);
-  const int qa = w, qb = 7 - w;      // qa < qb
+  constexpr int NQ = 2 * TT;         // query tiles
+  const int qa = w, qb = NQ - 1 - w;   // qa < qb (TT < 4: waves past TT have none)
+  if constexpr (TT < 4) {            // one block
+#pragma unroll
+    for (int hd = 0; hd < NH; ++hd) {
+      if (w == 0)
+        attn_short<DH, NQ, 0>(Qs, Ks, Vts, hd * DH, lane);
+      else if (TT >= 2 && w == 1)
+        attn_short<DH, NQ, TT >= 2 ? 1 : 0>(Qs, Ks, Vts, hd * DH, lane);
+      else if (TT >= 3 && w == 2)
+        attn_short<DH, NQ, TT >= 3 ? 2 : 0>(Qs, Ks, Vts, hd * DH, lane);
+    }
+    prime();
+    return;
+  }
 #pragma unroll
   for (int hd = 0; hd < NH; ++hd) {
     AttnState<DH> sa, sb;
@@ -777,13 +805,13 @@ __device__ __forceinline__ void attend_group(int g, int p0, bf16_t* Qs, const bf
     if constexpr (NM)
       attn_segment2<DH, -2, -2, 4, 4, true>(sa, sb, Ks, QLD, Vts, VLD, hd * DH, lane, kvl);
     else if (w == 0)
-      attn_own<DH, 0>(sa, sb, Ks, Vts, hd * DH, lane);
+      attn_own<DH, 8, 0>(sa, sb, Ks, Vts, hd * DH, lane);
     else if (w == 1)
-      attn_own<DH, 1>(sa, sb, Ks, Vts, hd * DH, lane);
+      attn_own<DH, 8, 1>(sa, sb, Ks, Vts, hd * DH, lane);
     else if (w == 2)
-      attn_own<DH, 2>(sa, sb, Ks, Vts, hd * DH, lane);
+      attn_own<DH, 8, 2>(sa, sb, Ks, Vts, hd * DH, lane);
     else
-      attn_own<DH, 3>(sa, sb, Ks, Vts, hd * DH, lane);
+      attn_own<DH, 8, 3>(sa, sb, Ks, Vts, hd * DH, lane);
     if (hd == NH - 1) prime();
     for (int c0 = 0; c0 < p0; c0 += BT) {     // earlier blocks: every key visible
       if (c0 > 0) cache_load(ch, kc, vc, tpad, g, c0);
@@ -796,7 +824,7 @@ __device__ __forceinline__ void attend_group(int g, int p0, bf16_t* Qs, const bf
   }
   // the next group's first cached chunk, in flight during this group's output
   // projection and the next group's Q / K / V
-  if (p0 > 0 && g + 1 < DM / 64) cache_load(ch, kc, vc, tpad, g + 1, 0);
+  if (TT == 4 && p0 > 0 && g + 1 < DM / 64) cache_load(ch, kc, vc, tpad, g + 1, 0);
 }
 
 __device__ __forceinline__ int64_t nl_of(const Args& A, int64_t n) { return n - A.c0; }
@@ -808,8 +836,9 @@ __device__ __forceinline__ int64_t nl_of(const Args& A, int64_t n) { return n - 
 // candidate half of the projection plus b_in) comes from cand_proj_kernel.  Rows
 // past the valid length get whatever these give (token rows of zeros): no valid
 // row ever reads them (causal mask, per-token sublayers, pooling over valid rows).
+template <int TT>
 __device__ __forceinline__ void encode_block_input(const Args& A, int64_t n, int p0, int Tv,
-                                                   f32x16 (&acc)[2][4], bf16_t* Xs,
+                                                   f32x16 (&acc)[2][TT], bf16_t* Xs,
                                                    int* tinfo, const uint8_t** rowptr, Pre& pre,
                                                    const WSeg& nxt) {
   const int d = A.d;
@@ -831,7 +860,7 @@ __device__ __forceinline__ void encode_block_input(const Args& A, int64_t n, int
   }
   {
     // all of the thread's row pieces in flight at once, then into LDS
-    constexpr int PER = BT * (KIN / 8) / NT;
+    constexpr int PER = 32 * TT * (KIN / 8) / NT;
     const int tid = otid();
     u32x4 v[PER];
 #pragma unroll
@@ -851,7 +880,7 @@ __device__ __forceinline__ void encode_block_input(const Args& A, int64_t n, int
         for (int j = 0; j < 4; ++j) {
           const float4 c4 = *reinterpret_cast<const float4*>(cv + 64 * w + ft * 32 + 8 * j + 4 * hf);
 #pragma unroll
-          for (int tt = 0; tt < 4; ++tt) {
+          for (int tt = 0; tt < TT; ++tt) {
             acc[ft][tt][4 * j] = c4.x;
             acc[ft][tt][4 * j + 1] = c4.y;
             acc[ft][tt][4 * j + 2] = c4.z;
@@ -881,7 +910,7 @@ __device__ __forceinline__ void encode_block_input(const Args& A, int64_t n, int
     FZ_LANE_VARS
     __syncthreads();   // every wave is past Xs (tokens) and tinfo
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
       for (int ft = 0; ft < 2; ++ft)
 #pragma unroll
@@ -967,30 +996,30 @@ typedef short s16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t relu2(uint32_t x) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, x), s16x2{0, 0}));
 }
-template <class Nxt>
+template <class Nxt, int TT>
 __device__ __forceinline__ void ffn1_phase(Pre& pre, const WSeg& cur, const WSeg& nxt,
                                            const bf16_t* Xs, bf16_t* Hs) {
   FZ_LANE_VARS
   constexpr int NKB = ShF1::NKB;
-  f32x16 ha[2][4];
+  f32x16 ha[2][TT];
   bf16x8 wq[NKB][2];
-  bf16x8 xq[NKB][4];
+  bf16x8 xq[NKB][TT];
   const bf16_t* arow = Xs + l32 * XLD + 8 * hf;
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt) xq[0][tt] = lfrag(arow + 32 * tt * XLD);
+  for (int tt = 0; tt < TT; ++tt) xq[0][tt] = lfrag(arow + 32 * tt * XLD);
 #pragma unroll
   for (int j = 0; j < NKB; ++j) {
     if (j + 1 < ShF1::NX) {
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) xq[j + 1][tt] = lfrag(arow + 32 * tt * XLD + (j + 1) * 16);
+      for (int tt = 0; tt < TT; ++tt) xq[j + 1][tt] = lfrag(arow + 32 * tt * XLD + (j + 1) * 16);
     } else if (j + 1 < NKB) {   // the bias k-block
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) xq[j + 1][tt] = bias_ones();
+      for (int tt = 0; tt < TT; ++tt) xq[j + 1][tt] = bias_ones();
     }
     {   // token tile by token tile (as in resid_phase)
       const bf16x8 a0 = stream_frag<ShF1>(wq, pre, j, 0), a1 = stream_frag<ShF1>(wq, pre, j, 1);
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
+      for (int tt = 0; tt < TT; ++tt) {
         ha[0][tt] = mfma32(a0, xq[j][tt], j == 0 ? f32x16{} : ha[0][tt]);
         ha[1][tt] = mfma32(a1, xq[j][tt], j == 0 ? f32x16{} : ha[1][tt]);
       }
@@ -1001,7 +1030,7 @@ __device__ __forceinline__ void ffn1_phase(Pre& pre, const WSeg& cur, const WSeg
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int hid = (2 * w + t) * 32 + 8 * j + 4 * hf;
@@ -1066,9 +1095,9 @@ __device__ __forceinline__ CacheStoreTail<NKB> cache_store(const Args& A, int g,
 // V^T into LDS (and K / V^T into the cache for later blocks), causal attention
 // per head, and acc += O_g W_o[:, group]^T.  The stream leaves primed with the
 // first FFN chunk of the layer.  NM: unmasked (keys at or past kvl are padding).
-template <bool LAST, bool NM>
+template <bool LAST, bool NM, int TT>
 __device__ __forceinline__ void attention_group(const Args& A, const tav2_layer& L,
-                                                const LayerPk& pk, f32x16 (&acc)[2][4], Pre& pre,
+                                                const LayerPk& pk, f32x16 (&acc)[2][TT], Pre& pre,
                                                 bf16_t* Xs, bf16_t* Qs, bf16_t* Ks, bf16_t* Vts,
                                                 bf16_t* Kc, bf16_t* Vc, bf16_t* kc, bf16_t* vc,
                                                 int p0, bool keep, int g, CacheChunk& ch, int kvl) {
@@ -1082,9 +1111,9 @@ __device__ __forceinline__ void attention_group(const Args& A, const tav2_layer&
   // the output projection's look-ahead is loaded during the attention
   const auto prime = [&] { seg_prime<Wo>(pre, so, otid() % WAVE); };
   if (A.dh == 64)
-    attend_group<64, NM>(g, p0, Qs, Ks, Vts, kc, vc, A.tpad, Kc, Vc, ch, prime, kvl);
+    attend_group<64, NM, TT>(g, p0, Qs, Ks, Vts, kc, vc, A.tpad, Kc, Vc, ch, prime, kvl);
   else
-    attend_group<32, NM>(g, p0, Qs, Ks, Vts, kc, vc, A.tpad, Kc, Vc, ch, prime, kvl);
+    attend_group<32, NM, TT>(g, p0, Qs, Ks, Vts, kc, vc, A.tpad, Kc, Vc, ch, prime, kvl);
   __syncthreads();
   // the output projection carries the cache stores (after its first k-block's
   // weight loads, so the next phase's first wait on its weights does not also wait
@@ -1102,19 +1131,19 @@ __device__ __forceinline__ void attention_group(const Args& A, const tav2_layer&
 }
 // The last head group is peeled out of the loop: the code after it (LayerNorm)
 // then sees exactly which weight loads are still in flight.
-template <bool NM>
+template <bool NM, int TT>
 __device__ __forceinline__ void attention_sublayer(const Args& A, const tav2_layer& L,
-                                                   const LayerPk& pk, f32x16 (&acc)[2][4],
+                                                   const LayerPk& pk, f32x16 (&acc)[2][TT],
                                                    Pre& pre, bf16_t* Xs,
                                                    bf16_t* Qs, bf16_t* Ks, bf16_t* Vts, bf16_t* Kc,
                                                    bf16_t* Vc, bf16_t* kc, bf16_t* vc, int p0,
                                                    bool keep, int kvl) {
   CacheChunk ch;   // first cached chunk of the group about to attend
-  if (p0 > 0) cache_load(ch, kc, vc, A.tpad, 0, 0);
+  if (TT == 4 && p0 > 0) cache_load(ch, kc, vc, A.tpad, 0, 0);
   for (int g = 0; g + 1 < DM / 64; ++g)
-    attention_group<false, NM>(A, L, pk, acc, pre, Xs, Qs, Ks, Vts, Kc, Vc, kc, vc, p0, keep, g,
+    attention_group<false, NM, TT>(A, L, pk, acc, pre, Xs, Qs, Ks, Vts, Kc, Vc, kc, vc, p0, keep, g,
                                ch, kvl);
-  attention_group<true, NM>(A, L, pk, acc, pre, Xs, Qs, Ks, Vts, Kc, Vc, kc, vc, p0, keep,
+  attention_group<true, NM, TT>(A, L, pk, acc, pre, Xs, Qs, Ks, Vts, Kc, Vc, kc, vc, p0, keep,
                             DM / 64 - 1, ch, kvl);
 }
 
@@ -1123,9 +1152,9 @@ __device__ __forceinline__ void attention_sublayer(const Args& A, const tav2_lay
 // primed with chunk 0 and leaves primed with `after`: the next layer's first
 // Q / K / V phase, or (last layer) the pooling projection (shape After).  The
 // last chunk is peeled out of the loop (see attention_sublayer).
-template <bool LAST, class After>
+template <bool LAST, class After, int TT>
 __device__ __forceinline__ void ffn_chunk(const Args& A, const tav2_layer& L, const LayerPk& pk,
-                                          f32x16 (&acc)[2][4], Pre& pre, const WSeg& after,
+                                          f32x16 (&acc)[2][TT], Pre& pre, const WSeg& after,
                                           const bf16_t* Xs, bf16_t* Hs, int c) {
   using F2 = typename std::conditional<LAST, ShF2L, ShF2>::type;
   const int w = __builtin_amdgcn_readfirstlane(otid() / WAVE);
@@ -1134,7 +1163,7 @@ __device__ __forceinline__ void ffn_chunk(const Args& A, const tav2_layer& L, co
   // weight loads and go past the hidden chunk before the second layer
   LnParams q;
   if constexpr (LAST) q = ln_params_load(L.ln2_g, L.ln2_b);
-  ffn1_phase<F2>(pre, seg_ffn1(pk.w1, c, w), s2, Xs, Hs);
+  ffn1_phase<F2, TT>(pre, seg_ffn1(pk.w1, c, w), s2, Xs, Hs);
   if constexpr (LAST)
     ln_params_store(q, reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(Hs) + BT * HLD * 2));
   __syncthreads();
@@ -1144,22 +1173,22 @@ __device__ __forceinline__ void ffn_chunk(const Args& A, const tav2_layer& L, co
     resid_phase<F2, After>(acc, pre, s2, after, Hs, HLD);
   __syncthreads();   // Hs is rewritten by the next chunk
 }
-template <class After>
+template <class After, int TT>
 __device__ __forceinline__ void ffn_sublayer(const Args& A, const tav2_layer& L,
-                                             const LayerPk& pk, f32x16 (&acc)[2][4], Pre& pre,
+                                             const LayerPk& pk, f32x16 (&acc)[2][TT], Pre& pre,
                                              const WSeg& after, bf16_t* Xs, bf16_t* Hs) {
   const int nch = A.ffn / FC;
   for (int c = 0; c + 1 < nch; ++c)
-    ffn_chunk<false, After>(A, L, pk, acc, pre, after, Xs, Hs, c);
-  ffn_chunk<true, After>(A, L, pk, acc, pre, after, Xs, Hs, nch - 1);
+    ffn_chunk<false, After, TT>(A, L, pk, acc, pre, after, Xs, Hs, c);
+  ffn_chunk<true, After, TT>(A, L, pk, acc, pre, after, Xs, Hs, nch - 1);
 }
 
 // One encoder layer of the block: attention, LayerNorm 1, FFN, LayerNorm 2.  The
 // last layer is a separate instance (its FFN leaves the stream primed with the
 // pooling projection instead of the next layer's Q / K / V), so that no code
 // joins two different look-ahead states.
-template <bool LASTL, bool NM>
-__device__ __forceinline__ void encoder_layer(const Args& A, int li, f32x16 (&acc)[2][4],
+template <bool LASTL, bool NM, int TT>
+__device__ __forceinline__ void encoder_layer(const Args& A, int li, f32x16 (&acc)[2][TT],
                                               Pre& pre, uint8_t* smem, int64_t nl, int p0,
                                               bool keep, int kvl) {
   const Args* AK = (const Args*)(__builtin_amdgcn_kernarg_segment_ptr());
@@ -1181,19 +1210,23 @@ __device__ __forceinline__ void encoder_layer(const Args& A, int li, f32x16 (&ac
   const LayerPk pk = AK->pk[li];
   bf16_t* kc = A.kcache ? A.kcache + (nl * A.n_layers + li) * int64_t(A.tpad) * DM : nullptr;
   bf16_t* vc = A.vcache ? A.vcache + (nl * A.n_layers + li) * int64_t(DM) * A.tpad : nullptr;
-  attention_sublayer<NM>(A, L, pk, acc, pre, Xs, Qs, Ks, Vts, Kc, Vc, kc, vc, p0, keep, kvl);
+  attention_sublayer<NM, TT>(A, L, pk, acc, pre, Xs, Qs, Ks, Vts, Kc, Vc, kc, vc, p0, keep, kvl);
   layer_norm(acc, lnp1, red, Xs);
   if constexpr (LASTL)
-    ffn_sublayer<ShPool>(A, L, pk, acc, pre, seg_resid(A.pk_pool, DM / 16, 0, w), Xs, Hs);
+    ffn_sublayer<ShPool, TT>(A, L, pk, acc, pre, seg_resid(A.pk_pool, DM / 16, 0, w), Xs, Hs);
   else
-    ffn_sublayer<ShQkv>(A, L, pk, acc, pre, seg_qkv(AK->pk[li + 1].qkv, 0, w), Xs, Hs);
+    ffn_sublayer<ShQkv, TT>(A, L, pk, acc, pre, seg_qkv(AK->pk[li + 1].qkv, 0, w), Xs, Hs);
   layer_norm(acc, lnp2, red, Xs);
 }
 
 // ---------------------------------------------------------------- the kernel
 // NM: the unmasked mode (every valid position sees every valid position; the
 // host allows it only when T fits one 128-position block).
-template <bool NM>
+// TT: 32-token tiles of a block.  4, or fewer where every candidate fits one lower
+// block (T <= 32 TT, the host's choice): the products' token loops shorten, the layout
+// in LDS stays.  Rows past 32 TT of the Q / K / V tiles are computed by the waves of
+// the second half from what LDS holds and never read.
+template <bool NM, int TT>
 __global__ __launch_bounds__(NT) void encoder_fused_kernel(Args A) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[LDS_BYTES];
   bf16_t* Xs = reinterpret_cast<bf16_t*>(smem);
@@ -1209,14 +1242,14 @@ __global__ __launch_bounds__(NT) void encoder_fused_kernel(Args A) {
     for (int c = threadIdx.x; c < 2 * DM; c += NT) out[c] = 0.f;
     return;
   }
-  const int nblk = (Tv + BT - 1) / BT;
+  const int nblk = (Tv + BT - 1) / BT;   // TT < 4: always one
   const Args* AK = (const Args*)(__builtin_amdgcn_kernarg_segment_ptr());
   const int wv = __builtin_amdgcn_readfirstlane(otid() / WAVE);
   const WSeg s_embed = seg_resid(A.pk_in, KIN / 16, 0, wv);
   const WSeg s_pool = seg_resid(A.pk_pool, DM / 16, 0, wv);
   Pre pre;
   seg_prime<ShEmb>(pre, s_embed, otid() % WAVE);
-  f32x16 acc[2][4];
+  f32x16 acc[2][TT];
   float pm = -__builtin_inff();   // running pooled max of feature pool_feature()
   for (int blk = 0; blk < nblk; ++blk) {
     const int p0 = blk * BT;
@@ -1224,15 +1257,15 @@ __global__ __launch_bounds__(NT) void encoder_fused_kernel(Args A) {
     encode_block_input(A, n, p0, Tv, acc, Xs, tinfo, rowptr, pre,
                        seg_qkv(AK->pk[0].qkv, 0, wv));
     for (int li = 0; li + 1 < A.n_layers; ++li)
-      encoder_layer<false, NM>(A, li, acc, pre, smem, nl, p0, blk + 1 < nblk, Tv - p0);
-    encoder_layer<true, NM>(A, A.n_layers - 1, acc, pre, smem, nl, p0, blk + 1 < nblk, Tv - p0);
+      encoder_layer<false, NM, TT>(A, li, acc, pre, smem, nl, p0, blk + 1 < nblk, Tv - p0);
+    encoder_layer<true, NM, TT>(A, A.n_layers - 1, acc, pre, smem, nl, p0, blk + 1 < nblk, Tv - p0);
     // ---- head: out[DM:] = X of the last valid token; running max of the pool
     {
       FZ_LANE_VARS
       const int last = Tv - 1 - p0;
       if (last >= 0 && last < BT) {
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
+        for (int tt = 0; tt < TT; ++tt)
           if (tt * 32 + l32 == last) {
 #pragma unroll
             for (int ft = 0; ft < 2; ++ft)
@@ -1249,7 +1282,7 @@ __global__ __launch_bounds__(NT) void encoder_fused_kernel(Args A) {
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = f32x16{};
+      for (int b = 0; b < TT; ++b) acc[a][b] = f32x16{};
     // the pool phase prefetches the next block's input projection (also after the
     // last block, where the loads are simply unused)
     resid_phase<ShPool, ShEmb>(acc, pre, s_pool, s_embed, Xs, XLD);
@@ -1267,5 +1300,8 @@ __global__ __launch_bounds__(NT) void encoder_fused_kernel(Args A) {
 // unit of its own, so that the causal kernel's code is generated as if it were
 // the only instantiation).
 hipError_t launch_encoder_fused_unmasked(const fz::Args& a, unsigned grid, hipStream_t st);
+
+// Launch of the instantiations for T <= 96 positions (encoder_fused_short.hip).
+hipError_t launch_encoder_fused_short(const fz::Args& a, int T, unsigned grid, hipStream_t st);
 
 }  // namespace tav2

@@ -7,7 +7,7 @@
 namespace tav2 {
 
 hipError_t launch_encoder_fused_unmasked(const fz::Args& a, unsigned grid, hipStream_t st) {
-  fz::encoder_fused_kernel<true><<<grid, fz::NT, 0, st>>>(a);
+  fz::encoder_fused_kernel<true, 4><<<grid, fz::NT, 0, st>>>(a);
   return hipGetLastError();
 }
 

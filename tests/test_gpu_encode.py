@@ -256,3 +256,14 @@ def test_packed_weights_equal_per_call_packing(k):
 def test_fp32_encoder_tile_edges(shape, flags):
     w = synth.scaled(synth.TINY, R=3, L=None, L_range=(1, 60), N=7, **shape)
     check_workload(w, flags=flags)
+
+
+@pytest.mark.parametrize("n_heads", [4, 8])
+@pytest.mark.parametrize("k", [1, 16, 17, 31, 32, 33, 48, 63, 64, 65, 80, 95, 96, 97])
+def test_bf16_block_heights(k, n_heads):
+    """d_model 256 with every block height (32, 64, 96, 128 tokens): the edges of the
+    blocks and of their 16-query tiles, requests longer and shorter than k."""
+    print(f"block heights k={k} heads={n_heads}", flush=True)
+    w = synth.scaled(synth.SINGLE, R=3, L=None, L_range=(max(1, k // 2), k + 30), N=5, k=k,
+                     n_heads=n_heads, n_layers=2)
+    check_workload(w)
