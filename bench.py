@@ -79,6 +79,8 @@ def site_work(w, total, valid_tokens, pairs, launches_per_step, rows_total, k):
     else:
         per["nn_filter"] = ("flop", 2.0 * pairs * d, None)
         per["nn_sample"] = ("flop", 2.0 * 1024 * d * total, None)
+    # the one-launch search of narrow rows: the same work
+    per["nn_resident"] = per["nn_filter"]
     out = {}
     for site, (kind, amount, mat) in per.items():
         n = launches_per_step.get(site)

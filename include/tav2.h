@@ -231,9 +231,8 @@ tav2_status tav2_gather(const tav2_seq* seq, const tav2_seq* rt, const tav2_cand
 
 /*
  * Packed encoder weights: the bf16 encoder reads its matrices and side tables in
- * its own fragment order (dm 64: the image of every layer weight, W_in's token
- * half and W_pool as the kernel holds them in LDS, which it then loads with one
- * contiguous copy).  tav2_pack_weights writes that form once into a
+ * its own fragment order (dm 64: the layer weights, W_in's token half and W_pool
+ * as operand fragments, which the kernel copies into LDS as they stand).  tav2_pack_weights writes that form once into a
  * caller-owned device buffer of tav2_pack_weights_bytes(w) bytes (256-byte
  * aligned); a tav2_weights whose `packed` points at it skips the packing step
  * of every later call (the paper's serving engine likewise keeps its model in

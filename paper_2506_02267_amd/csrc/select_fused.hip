@@ -16,8 +16,8 @@
 //     one global counter update per candidate and workgroup);
 //  4. select: per candidate, when the list holds at least k values and did not
 //     overflow, every one of the k best rows is in it (at least k keys are >= t,
-//     so the k-th largest key is >= t); a radix select over the list finds them
-//     and they are placed by rank.  Otherwise the candidate is queued;
+//     so the k-th largest key is >= t); they are placed by bins (a radix select
+//     and placement by rank where many scores are equal).  Otherwise the candidate is queued;
 //  5. fallback: each queued candidate's scores are recomputed into LDS with the
 //     same products (bit-identical keys) and searched exhaustively.
 // The result is exact in every case; the threshold only decides how much work

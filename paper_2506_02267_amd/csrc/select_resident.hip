@@ -125,7 +125,7 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
   if (n >= A.cand_off[r + 1]) return;
   const int tid = threadIdx.x, lane = tid % WAVE, hf = lane / 32;
   if (A.cand_req && tid == 0) A.cand_req[n] = r;   // the candidate's request, for the encoder
-  const int L = min(A.seq_len[r], A.max_len);
+  const int L = max(0, min(A.seq_len[r], A.max_len));
   const int k = A.k, kk = k < L ? k : L;
   int32_t* oi = A.out_idx + n * A.out_ld;
   float* os = A.out_score + n * A.out_ld;
