@@ -272,3 +272,48 @@ def test_resident_rows(dtype, d, L, k, ties):
     torch.cuda.synchronize()
     ref_i, ref_s = oracle_select(inp, k)
     assert_select_equal(idx, score, ref_i, ref_s)
+
+
+@pytest.mark.parametrize("dtype,d", [("i8", 32), ("bf16", 32), ("i8", 64)])
+@pytest.mark.parametrize("L", [700, 3000, 5000, 8192])
+def test_resident_equals_the_general_search(dtype, d, L):
+    """The same candidates alone (every product in registers) and three times over (too
+    many for that): bit for bit the same, also for infinite, huge, tiny, zero and
+    not-a-number candidates."""
+    print(f"resident against general {dtype} d={d} L={L}", flush=True)
+    g = torch.Generator().manual_seed(L + d)
+    n, k = 200, 100
+    if dtype == "i8":
+        emb = torch.randint(-127, 128, (2 * L, d), generator=g, dtype=torch.int8)
+        emb[5] = 0                                # a row without a norm
+    else:
+        emb = torch.randn(2 * L, d, generator=g).bfloat16()
+    cand = torch.randn(n, d, generator=g)
+    cand[0] = 0.0
+    cand[1, 3] = float("inf")
+    cand[2, 4] = -float("inf")
+    cand[3] *= 1e38
+    cand[4] *= 1e-39
+    cand[5, 0] = float("nan")
+    cand[6, :2] = torch.tensor([float("inf"), -float("inf")])
+    cand = cand.bfloat16().cuda()
+    seq = T.DeviceSeq(emb=emb.cuda(), act=torch.zeros(2 * L, dtype=torch.uint8, device="cuda"), time=None,
+                      offset=torch.tensor([L, 0], device="cuda"),
+                      length=torch.tensor([L, L - 37], dtype=torch.int32, device="cuda"), max_len=L,
+                      dtype=T.I8 if dtype == "i8" else T.BF16)
+
+    def search(c, per):
+        off = torch.tensor([0, per, 2 * per], device="cuda")
+        i, s = T.nn_select(seq, T.DeviceCands(emb=c, offset=off, max_count=per), k)
+        torch.cuda.synchronize()
+        return i.cpu(), s.cpu().view(torch.int32)
+
+    h = n // 2
+    i1, s1 = search(cand, h)
+    big = torch.cat([cand[:h]] * 3 + [cand[h:]] * 3)
+    i3, s3 = search(big, 3 * h)
+    for r in range(2):
+        for rep in range(3):
+            a, b = slice(r * h, r * h + h), slice((3 * r + rep) * h, (3 * r + rep + 1) * h)
+            assert torch.equal(i1[a], i3[b])
+            assert torch.equal(s1[a], s3[b])
