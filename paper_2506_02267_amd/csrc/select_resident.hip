@@ -98,17 +98,18 @@ __device__ __noinline__ void place_by_bits(const uint32_t* key, int kk, uint32_t
 
 // A row's score from its product (and, for codes, its sum of squares): exact, and the
 // estimate through the hardware reciprocal square root.  The two have the same sign and
-// keys at most SLACK apart (relative error below 2^-21); a product that is not a number
-// is its own score in both.
+// keys at most SLACK apart (relative error below 2^-21); an all-zero row scores 0 whatever
+// its product (0 x inf), and of the other rows a product that is not a number is its own
+// score in both.
 constexpr uint32_t SLACK = 64;
 template <bool I8>
 __device__ __forceinline__ uint32_t exact_key(float dot, float ss) {
-  return score_key(I8 && dot == dot ? i8_score(dot, ss) : dot);
+  return score_key(I8 && (dot == dot || !(ss > 0.f)) ? i8_score(dot, ss) : dot);
 }
 template <bool I8>
 __device__ __forceinline__ uint32_t estimate_key(float dot, float ss) {
   const float est = ss > 0.f ? dot * __builtin_amdgcn_rsqf(ss) : 0.f;
-  return score_key(I8 && dot == dot ? est : dot);
+  return score_key(I8 && (dot == dot || !(ss > 0.f)) ? est : dot);
 }
 
 // NT threads, RPT rows per thread (the rows fit NT x RPT), d = 16 KB.

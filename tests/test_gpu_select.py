@@ -275,17 +275,18 @@ def test_resident_rows(dtype, d, L, k, ties):
 
 
 @pytest.mark.parametrize("dtype,d", [("i8", 32), ("bf16", 32), ("i8", 64)])
-@pytest.mark.parametrize("L", [700, 3000, 5000, 8192])
+@pytest.mark.parametrize("L", [90, 700, 3000, 5000, 8192])
 def test_resident_equals_the_general_search(dtype, d, L):
     """The same candidates alone (every product in registers) and three times over (too
     many for that): bit for bit the same, also for infinite, huge, tiny, zero and
-    not-a-number candidates."""
+    not-a-number candidates, over requests with an all-zero row each (int8: its score is 0
+    whatever the candidate)."""
     print(f"resident against general {dtype} d={d} L={L}", flush=True)
     g = torch.Generator().manual_seed(L + d)
     n, k = 200, 100
     if dtype == "i8":
         emb = torch.randint(-127, 128, (2 * L, d), generator=g, dtype=torch.int8)
-        emb[5] = 0                                # a row without a norm
+        emb[[5, L + 5]] = 0                       # a row without a norm in each request
     else:
         emb = torch.randn(2 * L, d, generator=g).bfloat16()
     cand = torch.randn(n, d, generator=g)
@@ -317,3 +318,9 @@ def test_resident_equals_the_general_search(dtype, d, L):
             a, b = slice(r * h, r * h + h), slice((3 * r + rep) * h, (3 * r + rep + 1) * h)
             assert torch.equal(i1[a], i3[b])
             assert torch.equal(s1[a], s3[b])
+    if dtype == "i8":
+        # request 0's seven extreme candidates: wherever its zero row was selected, it scored 0
+        hit = (i1[:7] == 5)
+        assert torch.all(s1[:7][hit] == 0)
+        if k >= L:
+            assert torch.all(hit.any(1))
