@@ -467,8 +467,7 @@ template <int DH>
 struct Att {
   bf16x8 qf[DH / 32];   // Q^T fragments
   f32x4 o[DH / 16];     // O^T accumulators
-  f32x4 l;              // row sums of P (element 0; the product with a row of ones)
-  float m;              // reference of the exponents (log2 units)
+  float m, l;           // reference of the exponents (log2 units), this lane's partial row sum
 };
 // A pair of 32 keys at kv (fragments), head h: the K operands, S^T = K Q^T (one query
 // per lane column; key 16 t + 4 g + i in s[t][i]), and the V^T operands.
@@ -521,20 +520,20 @@ __device__ __forceinline__ void add_pair(Att<DH>& st, const f32x4 (&s)[2], const
     const float mnew = vmax(st.m, xmax32(xmax16(mx)) * sc);
     const float alpha = __builtin_amdgcn_exp2f(st.m - mnew);
     st.m = mnew;
-    st.l[0] *= alpha;
+    st.l *= alpha;
 #pragma unroll
     for (int dt = 0; dt < DH / 16; ++dt) st.o[dt] *= alpha;
   }
-  const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
   f32x4 e[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int i = 0; i < 4; ++i) e[t][i] = __builtin_amdgcn_exp2f(fmaf(s[t][i], sc, -st.m));
+  // the row sums are those of the exponentials in fp32, before P is rounded
+  st.l += ((e[0][0] + e[0][1]) + (e[0][2] + e[0][3])) + ((e[1][0] + e[1][1]) + (e[1][2] + e[1][3]));
   const bf16x8 pb = pack8(e[0], e[1]);
 #pragma unroll
   for (int dt = 0; dt < DH / 16; ++dt) st.o[dt] = mma(v[dt], pb, st.o[dt]);
-  st.l = mma(ones, pb, st.l);
 }
 // Pairs `first` (if >= 0; masked by lim) and then 0 .. np - 1 (every key visible),
 // each pair's scores taken while the pair before it is added.
@@ -728,7 +727,7 @@ __global__ __launch_bounds__(NW* WAVE) void encoder_small_kernel(Args A) {
 #pragma unroll
             for (int dt = 0; dt < DH / 16; ++dt) st[h].o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
             st[h].m = -__builtin_inff();
-            st[h].l = f32x4{0.f, 0.f, 0.f, 0.f};
+            st[h].l = 0.f;
             if (A.unmasked) {   // one block: every valid key
               for (int q = 0; 32 * q < Tv; ++q) {
                 bf16x8 k[2][DH / 32], v[DH / 16];
@@ -790,7 +789,7 @@ __global__ __launch_bounds__(NW* WAVE) void encoder_small_kernel(Args A) {
           fence();
 #pragma unroll
           for (int h = 0; h < NH; ++h) {
-            const float inv = 1.f / st[h].l[0];
+            const float inv = 1.f / xsum32(xsum16(st[h].l));
 #pragma unroll
             for (int dt = 0; dt < DH / 16; ++dt) st[h].o[dt] *= inv;
 #pragma unroll

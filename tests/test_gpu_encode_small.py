@@ -188,3 +188,71 @@ def test_tables_aligned_to_8_bytes_only():
         kept.append(buf)
         setattr(dw.s, name, buf.data_ptr() + 8)
     assert torch.equal(T.encode(tok, cand, dw), ref)
+
+
+def one_value_inputs(T_, n_heads, total=3):
+    """Tokens and weights (one layer, d 64) whose last query's attention output is one
+    value V over the softmax's sum: its own key scores 0 (weight exactly 1), every other key
+    has V = 0 and a weight just under the midpoint of 1/2 and the next bf16, 0.4 % above
+    what it rounds to.  Returns the batch, the weights and the exact last rows (float64, the
+    attention output rounded once to bf16, as the kernel's output projection takes it)."""
+    dm, dh = 64, 64 // n_heads
+    W = weights_for(T_, d=dm, n_heads=n_heads, n_layers=1)
+    for a in (W.b_in, W.E_act, W.E_time, W.E_pos, W.b_pool):
+        a[:] = 0
+    W.W_in[:] = np.concatenate([np.eye(dm), np.zeros((dm, dm))], axis=1)
+    L = W.layers[0]
+    for a in (L.W_qkv, L.b_qkv, L.b_o, L.W_1, L.b_1, L.W_2, L.b_2, L.ln1_b, L.ln2_b):
+        a[:] = 0
+    L.ln1_g[:] = L.ln2_g[:] = 1
+    L.W_o[:] = np.eye(dm)
+    bf = synth.round_to_bf16
+    # score of the other keys: x[1] + x[2] through the head's first two dimensions
+    t = np.log(0.5 + 2.0 ** -9 - 2.0 ** -13) * np.sqrt(dh)
+    hi = float(bf(np.array([t], np.float32))[0])
+    lo = float(bf(np.array([t - hi], np.float32))[0])
+    p = np.exp((hi + lo) / np.sqrt(dh))
+    for h in range(n_heads):
+        L.b_qkv[h * dh:h * dh + 2] = 1
+        L.W_qkv[dm + h * dh, 1] = L.W_qkv[dm + h * dh + 1, 2] = 1
+    vl = np.array([T_, T_ - 1, T_ - 2])[:total].astype(np.int32)
+    emb = np.zeros((total, T_, dm), np.float32)
+    emb[:, :, 1], emb[:, :, 2] = hi, lo
+    # V: of the bf16 between 1.5 l and 1.97 l the one whose V / l lies nearest to a bf16 (its
+    # rounding then hangs on no last bits, and 0.36 % more is past the midpoint to the next)
+    last = np.where(np.arange(dm) % 2, 1.0, -0.5)
+    last[0], last[1:3] = 1, 0
+    exact = []
+    for n in range(total):
+        l = 1 + (vl[n] - 1) * p
+        v = np.unique(bf(np.linspace(1.5 * l, 1.97 * l, 800).astype(np.float32))).astype(np.float64)
+        o = bf((v / l).astype(np.float32)).astype(np.float64)
+        best = int(np.argmin(np.abs(v / l - o)))
+        assert abs(v[best] / l - o[best]) < 2.0 ** -10 * 0.9   # a spacing is 2^-7, a midpoint 2^-8
+        emb[n, vl[n] - 1] = last
+        emb[n, vl[n] - 1, 0] = v[best]
+        # V = x[0] in the upper half of every head
+        up = np.arange(dm) % dh >= dh // 2
+        L.W_qkv[2 * dm + np.flatnonzero(up), 0] = 1
+        x = emb[n, vl[n] - 1].astype(np.float64) + up * o[best]
+        for _ in range(2):
+            x = (x - x.mean()) / np.sqrt(x.var() + 1e-5)
+        exact.append(x)
+    tb = synth.make_tokens(total, T_, dm, seed=1, valid_len=vl)
+    tb.emb[:], tb.cand[:] = emb, 0
+    return tb, W, np.array(exact)
+
+
+@pytest.mark.parametrize("n_heads", [1, 2])
+@pytest.mark.parametrize("T_", [20, 64, 190, 192, 300])
+def test_softmax_sums_are_not_rounded(T_, n_heads):
+    """The softmax's row sums are sums of fp32 exponentials: summed after their rounding
+    to bf16 they would be 0.4 % too small here, and the attention output the next bf16.
+    Bound: fp32 arithmetic on values below 8 (2^-20), against 2e-3 for that fault."""
+    print(f"encode_small softmax sums T={T_} heads={n_heads}", flush=True)
+    tb, W, exact = one_value_inputs(T_, n_heads)
+    tok, cand = upload_tokens(tb)
+    out = T.encode(tok, cand, T.DeviceWeights(W)).cpu().numpy().astype(np.float64)
+    err = np.abs(out[:, 64:] - exact).max()
+    print(f"  max abs error {err:.3e}", flush=True)
+    assert err <= 2e-5
