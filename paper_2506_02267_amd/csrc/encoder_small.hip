@@ -506,11 +506,13 @@ __device__ __forceinline__ void mask_scores(f32x4 (&s)[2], int lim) {
 // The pair's weights and its share of O and of the row sums.  The reference of the
 // exponents is raised to the maximum, and the sums rescaled, only where a score has
 // grown past it by more than RAISE (then P stays below 2^RAISE, and its bf16
-// rounding and the 32-bit sums keep their relative precision).  A query's first
-// pair holds a visible key, so the reference is finite from then on.  exp2 is the
+// rounding and the 32-bit sums keep their relative precision).  It starts below every
+// score and is finite: keys whose scores are -inf get weight 0 also before the first
+// other one (-inf as the reference would make them not a number).  exp2 is the
 // hardware instruction (results below 2^-126 flush to zero, far under the bf16
 // resolution of P).
 constexpr float RAISE = 6.f;
+constexpr float NO_KEY = -3e38f;
 template <int DH>
 __device__ __forceinline__ void add_pair(Att<DH>& st, const f32x4 (&s)[2], const bf16x8 (&v)[DH / 16]) {
   constexpr float sc = (DH == 64 ? 0.125f : 0.17677669529663688f) * 1.4426950408889634f;
@@ -726,7 +728,7 @@ __global__ __launch_bounds__(NW* WAVE) void encoder_small_kernel(Args A) {
           for (int h = 0; h < NH; ++h) {
 #pragma unroll
             for (int dt = 0; dt < DH / 16; ++dt) st[h].o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            st[h].m = -__builtin_inff();
+            st[h].m = NO_KEY;
             st[h].l = 0.f;
             if (A.unmasked) {   // one block: every valid key
               for (int q = 0; 32 * q < Tv; ++q) {

@@ -256,3 +256,25 @@ def test_softmax_sums_are_not_rounded(T_, n_heads):
     err = np.abs(out[:, 64:] - exact).max()
     print(f"  max abs error {err:.3e}", flush=True)
     assert err <= 2e-5
+
+
+@pytest.mark.parametrize("T_,flags", [(64, T.MASK_CAUSAL), (64, T.MASK_NONE), (300, T.MASK_CAUSAL)])
+def test_scores_that_overflow_downwards(T_, flags):
+    """Keys whose scores are below the fp32 range (-inf) have weight 0, also where the first
+    32 keys that a query looks at are all of that kind (causal: the 32 around its own
+    position; unmasked: the first 32)."""
+    print(f"encode_small overflowing scores T={T_} flags={flags}", flush=True)
+    W = weights_for(T_, d=64, n_layers=1, seed=9)
+    L = W.layers[0]
+    W.W_in[:] = np.concatenate([np.eye(64), np.zeros((64, 64))], axis=1)
+    for a in (W.b_in, W.E_act, W.E_time, W.E_pos):
+        a[:] = 0
+    L.W_qkv[:64], L.b_qkv[:128] = 0, 0
+    L.W_qkv[64:128] = 0
+    L.W_qkv[64, 1], L.b_qkv[0] = -1e20, 1e20      # score -1e40 x[1]
+    L.W_qkv[:] = synth.round_to_bf16(L.W_qkv)
+    L.W_qkv[128:] *= 16
+    tb = synth.make_tokens(4, T_, 64, seed=6, valid_len=[T_, T_ - 1, T_ - 9, 40])
+    p = np.arange(T_)
+    tb.emb[:, :, 1] = (p < 32) if flags == T.MASK_NONE else (p % 64 >= 32)
+    run_and_check(tb, W, flags=flags)
