@@ -111,6 +111,18 @@ __device__ __forceinline__ void load_vec(f32x4 (&v)[DT], const float* p, int n) 
   for (int f = 0; f < DT; ++f)
     v[f] = 16 * f + k0 < n ? *reinterpret_cast<const f32x4*>(p + 16 * f + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
 }
+// The same of a side table's row: tables are float-aligned only (unlike the vectors and
+// matrices); one 16-byte load all the same, which this GPU takes at any 4 bytes.
+typedef float f32x4_4 __attribute__((ext_vector_type(4), aligned(4)));
+template <int DT>
+__device__ __forceinline__ void load_row(f32x4 (&v)[DT], const float* p, int n) {
+  const int k0 = 4 * (threadIdx.x % WAVE / 16);
+#pragma unroll
+  for (int f = 0; f < DT; ++f) {
+    v[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (16 * f + k0 < n) v[f] = *reinterpret_cast<const f32x4_4*>(p + 16 * f + k0);
+  }
+}
 // x <- LayerNorm(x) over the dm features of the lane's token (padding features stay 0).
 template <int DT>
 __device__ __forceinline__ void layer_norm(f32x4 (&x)[DT], const f32x4 (&gain)[DT],
@@ -179,12 +191,12 @@ __global__ __launch_bounds__(MAX_NW* WAVE) void encode_f32_kernel(Args A) {
     // ---- Eq. 4 with early fusion: [e_p ; e_c] W_in^T + b_in + side tables
     f32x4 ta[DT], tp[DT];
     load_vec<DT>(x, A.b_in, dm);
-    load_vec<DT>(ta, A.E_act + t.act * dm, dm);
-    load_vec<DT>(tp, A.E_pos + (p < Tv ? p : Tv - 1) * dm, dm);
+    load_row<DT>(ta, A.E_act + t.act * dm, dm);
+    load_row<DT>(tp, A.E_pos + (p < Tv ? p : Tv - 1) * dm, dm);
 #pragma unroll
     for (int f = 0; f < DT; ++f) x[f] += ta[f] + tp[f];
     if (A.E_time) {
-      load_vec<DT>(ta, A.E_time + t.time * dm, dm);
+      load_row<DT>(ta, A.E_time + t.time * dm, dm);
 #pragma unroll
       for (int f = 0; f < DT; ++f) x[f] += ta[f];
     }

@@ -8,7 +8,7 @@ import torch
 import oracle
 import synth
 from helpers import (BF16_TOL, F32_TOL, assert_select_equal, max_abs, oracle_select_encode,
-                     strided_ids, upload)
+                     strided_ids, upload, upload_tokens)
 from paper_2506_02267_amd import tav2 as T
 
 pytestmark = pytest.mark.gpu
@@ -267,3 +267,21 @@ def test_bf16_block_heights(k, n_heads):
     w = synth.scaled(synth.SINGLE, R=3, L=None, L_range=(max(1, k // 2), k + 30), N=5, k=k,
                      n_heads=n_heads, n_layers=2)
     check_workload(w)
+
+
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_fp32_tables_aligned_to_floats_only(off):
+    """The float32 encoder's side tables may start at any float: the same bits."""
+    print(f"fp32 tables at +{4 * off} bytes", flush=True)
+    tb = synth.make_tokens(9, 33, 32, seed=3, valid_len=[33, 1, 0, 16, 17, 32, 5, 31, 2])
+    tok, cand = upload_tokens(tb, T.F32)
+    dw = T.DeviceWeights(synth.make_weights(synth.scaled(synth.TINY, d=32, k=33, has_time=True)))
+    ref = T.encode(tok, cand, dw).clone()
+    kept = []
+    for name in ("E_act", "E_time", "E_pos"):
+        src = next(t for t in dw.keep if t.data_ptr() == getattr(dw.s, name))
+        buf = torch.empty(src.numel() + off, dtype=src.dtype, device=src.device)
+        buf[off:].copy_(src.reshape(-1))
+        kept.append(buf)
+        setattr(dw.s, name, buf.data_ptr() + 4 * off)
+    assert torch.equal(T.encode(tok, cand, dw), ref)
