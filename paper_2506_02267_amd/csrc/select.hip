@@ -10,13 +10,13 @@
 // Top-k, one workgroup per candidate, scores as order-preserving 32-bit keys.
 // Rows of up to 4096 keys: the row is held in registers and its k best keys are
 // placed by bins (place_by_bins); where many keys are equal, the k-th largest key is
-// found by a 32-step bitwise search (each step one block-wide count), every key
-// above it kept plus the lowest-indexed rows equal to it (an ordered compaction
-// by block-wide prefix sum).  Longer rows are streamed once against a threshold
+// found bit by bit within the bounds that the bins gave (each step one block-wide
+// count), every key above it kept plus the lowest-indexed rows equal to it, which go
+// straight to their places (an ordered compaction by block-wide prefix sum).  Longer rows are streamed once against a threshold
 // taken from a sample, the keys above it compacted into LDS and the k-th largest
 // found there by a radix select (an exact streaming search when the sample
-// gives no usable threshold).  Either way the k survivors are placed by counting,
-// for each, how many survivors precede it in the total order.
+// gives no usable threshold).  Survivors that are not placed by bins are placed by
+// counting, for each, how many survivors precede it in the total order.
 #include <atomic>
 
 #include "common.h"
@@ -300,13 +300,14 @@ __global__ __launch_bounds__(256) void score_f32_kernel(
 // ---------------------------------------------------------------- top-k
 // NT: threads of a workgroup, PT: keys per thread (4 consecutive rows at a time).
 
-// Exclusive prefix (in thread order) and block total of NV 64-bit values per
-// thread; sw holds NV per wave.  sw is read after the one barrier inside: the
-// caller synchronizes again before sw is written by a later scan.
 // At most this many candidates (two per CU): 512 threads each, half as many keys per
 // thread (100 candidates of 2000 rows, k 256: 13.5 us a search against 17.3; more
 // candidates hide the latency themselves: 2800 of 4000 rows 33.8 against 39.7).
 constexpr int TK_WIDE = 512;
+
+// Exclusive prefix (in thread order) and block total of NV 64-bit values per
+// thread; sw holds NV per wave.  sw is read after the one barrier inside: the
+// caller synchronizes again before sw is written by a later scan.
 template <int NV, int NT>
 __device__ __forceinline__ void block_excl_scan(const uint64_t (&v)[NV], uint64_t (&excl)[NV],
                                                 uint64_t (&total)[NV], uint64_t* sw, int lane,
@@ -386,6 +387,7 @@ __global__ __launch_bounds__(NT) void topk_kernel(
       for (int u = 0; u < 4; ++u) key[4 * c + u] = (r0 + u < L) ? score_key(srow[r0 + u]) : 0u;
     }
   }
+  uint32_t tlo, thi;   // bounds of the kk-th best key
   {
     // the kk-th best key is at least the kk-th best of the threads' largest keys, so the
     // bins need not reach below the smallest of those when there are kk of them
@@ -399,18 +401,18 @@ __global__ __launch_bounds__(NT) void topk_kernel(
     if (few) lo = hi;
     block_min_max<NT>(lo, hi, bred);
     __syncthreads();   // bred is reused
-    const uint32_t least = lo;
-    if (place_by_bins<NT, PT>(
-            [&](int e) { return key[e] >= least ? key[e] : 0u; },
-            [&](int e) { return (e / 4) * CH + tid * 4 + e % 4; }, lo, hi, kk, hist, bred, sel, oi, os))
+    if (place_by_bins<NT, PT, true>([&](int e) { return key[e]; },
+                                    [&](int e) { return (e / 4) * CH + tid * 4 + e % 4; }, lo, hi, kk, hist,
+                                    bred, sel, oi, os, tlo, thi))
       return;
     __syncthreads();   // bred, sel: nothing of them is read any more
   }
 
-  {
-  // exhaustive: largest threshold t with count(key >= t) >= kk, one bit at a time
-  uint32_t thr = 0;
-  for (int b = 31; b >= 0; --b) {
+  // exhaustive: largest threshold t with count(key >= t) >= kk, one bit at a time below
+  // the bits that its bounds have in common
+  const int top = tlo == thi ? -1 : 31 - __builtin_clz(tlo ^ thi);
+  uint32_t thr = top < 0 ? tlo : top == 31 ? 0u : tlo & ~((2u << top) - 1u);
+  for (int b = top; b >= 0; --b) {
     const uint32_t probe = thr | (1u << b);
     // wave-level count: one compare per key, the lane mask counted on the scalar unit
     int cnt = 0;
@@ -424,8 +426,8 @@ __global__ __launch_bounds__(NT) void topk_kernel(
     if (tot >= kk) thr = probe;
   }
 
-  // compaction: keys above thr anywhere in sel[0, count_gt) (the rank sort orders
-  // them), then the need_eq lowest rows whose key equals thr.  Rows are ordered by
+  // Keys above thr go to sel[0, count_gt) in any order.  The need_eq lowest rows whose key
+  // equals thr follow them in row order, at their final places.  Rows are ordered by
   // (chunk, thread, u), so the equal keys are counted per chunk: 16-bit fields,
   // four chunks per 64-bit word, summed in one block scan with the above count.
   constexpr int NW = (NC + 3) / 4;
@@ -443,6 +445,7 @@ __global__ __launch_bounds__(NT) void topk_kernel(
   block_excl_scan<NW + 1, NT>(word, excl, total, scan_w, lane, wid);
   const int count_gt = int(total[0]);
   const int need_eq = kk - count_gt;
+  const float thr_score = key_score(thr);
   int gpos = int(excl[0]);
   int eq_before = 0;   // equal keys in chunks before c, over all threads
 #pragma unroll
@@ -453,34 +456,20 @@ __global__ __launch_bounds__(NT) void topk_kernel(
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const uint32_t kv = key[4 * c + u];
-      const uint32_t row = uint32_t(c * CH + tid * 4 + u);
-      const uint64_t packed = (uint64_t(kv) << 32) | uint64_t(0xFFFFFFFFu - row);
+      const int row = c * CH + tid * 4 + u;
       if (kv > thr) {
-        sel[gpos++] = packed;
+        sel[gpos++] = sel_value(kv, row);
       } else if (kv == thr) {
-        if (e < need_eq) sel[count_gt + e] = packed;
+        if (e < need_eq) {
+          oi[count_gt + e] = row;
+          os[count_gt + e] = thr_score;
+        }
         ++e;
       }
     }
   }
   __syncthreads();
-  }
-
-  // survivors are distinct under (key, -row): rank = number of survivors before it
-  for (int s = tid; s < kk; s += NT) {
-    const uint64_t me = sel[s];
-    int rank = 0;
-    // 8 independent LDS reads per iteration (the survivor count is not a
-    // multiple of 8 in general: the tail is handled one by one)
-    int t = 0;
-    for (; t + 8 <= kk; t += 8) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) rank += sel[t + u] > me ? 1 : 0;
-    }
-    for (; t < kk; ++t) rank += sel[t] > me ? 1 : 0;
-    oi[rank] = int32_t(0xFFFFFFFFu - uint32_t(me));
-    os[rank] = key_score(uint32_t(me >> 32));
-  }
+  place_by_rank<NT>(sel, count_gt, oi, os);
 }
 
 // ---------------------------------------------------------------- top-k, long rows

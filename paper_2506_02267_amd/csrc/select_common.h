@@ -224,14 +224,26 @@ __device__ __forceinline__ void place_by_rank(const uint64_t* sel, int kk, int32
 // by bit over the whole workgroup: 2800 candidates of 200 to 4000 rows at kk = 64, 62
 // and 31.)
 //
+// Bins as wide as the whole range are too coarse where it is wide (scores of both signs:
+// four bins to a factor of two), so the range is narrowed to what lies at or above the
+// kk-th value's bin, and binned again, while that makes the bins finer and that bin holds
+// more than a few values, or fewer than half of what it held (it does not shrink where it
+// holds equal scores).  Scores of both signs, rows of 16: 1000 candidates of 4000 rows at
+// kk = 256 and 700 at kk = 1000 take 22 and 23 us a search, and 56 and 103 with the first
+// pass's bins (37 and 81 by the bitwise search and counting).  NARROW off: one pass, for
+// keys that are known to lie above a close bound (the loop costs 22 registers there).
+//
 // key(e), row(e): the thread's elements e = 0 .. PER - 1 (key(e) = 0: none).  kmin,
-// kmax: bounds of the workgroup's keys, the same for every thread.  hist (1024 words,
-// zeroed, 16-byte aligned) and red (NT / 64 + 2 words) are LDS scratch; sorted holds at
-// least kk + BIN_MOST - 1 values.  The caller synchronises before (hist is zero).
+// kmax: bounds of the workgroup's keys, the same for every thread; keys below kmin are left
+// out (at least kk are not).  hist (1024 words, zeroed, 16-byte aligned) and red (NT / 64
+// + 3 words) are LDS scratch; sorted holds at least kk + BIN_MOST - 1 values.  The caller
+// synchronises before (hist is zero).
 // Returns false, with nothing written, when there is no kk-th value or its bin holds
-// more than BIN_MOST values (many equal scores): the caller then selects another way.
+// more than BIN_MOST values (many equal scores): the caller then selects another way, and
+// knows that the kk-th key lies in [tlo, thi].
 constexpr int NBINS = 1024;
 constexpr int BIN_MOST = 512;
+constexpr int BIN_FEW = 32;
 // Bins of one width over the keys kmin .. kmax, the largest keys first.
 struct KeyBins {
   uint32_t kmax;
@@ -242,14 +254,32 @@ struct KeyBins {
     shift = bits > 10 ? bits - 10 : 0;
   }
   __device__ __forceinline__ uint32_t operator()(uint32_t k) const { return (kmax - k) >> shift; }
+  // the largest and the smallest key of bin b (the smallest: not below kmin)
+  __device__ __forceinline__ uint32_t top(uint32_t b) const { return kmax - (b << shift); }
+  __device__ __forceinline__ uint32_t bottom(uint32_t b, uint32_t kmin) const {
+    const uint64_t past = (uint64_t(b) + 1) << shift;
+    return past > uint64_t(kmax - kmin) ? kmin : kmax - uint32_t(past) + 1u;
+  }
 };
+// One more value in bin b of hist.  Lanes that all count into one bin (equal scores) do so
+// at once: an LDS atomic takes its lanes' additions to one word one after the other.
+__device__ __forceinline__ void count_in_bin(uint32_t* hist, uint32_t b) {
+  const uint32_t b0 = uint32_t(__builtin_amdgcn_readfirstlane(int(b)));
+  const uint64_t in = __builtin_amdgcn_ballot_w64(true);
+  if (__builtin_amdgcn_ballot_w64(b == b0) == in) {
+    if (__builtin_amdgcn_mbcnt_hi(uint32_t(in >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(in), 0)) == 0)
+      atomicAdd(&hist[b0], uint32_t(__popcll(in)));
+  } else {
+    atomicAdd(&hist[b], 1u);
+  }
+}
 // hist (complete: the caller has synchronised) becomes its exclusive prefix; returns
 // the bin that holds the need-th value (need >= 1) with `end` the values up to that
-// bin's end, or ~0 if there are fewer or that bin holds more than `most`.
-// red: NT / 64 + 2 words.  Ends with a barrier.
+// bin's end and `cnt` its own, or ~0 if there are fewer.
+// red: NT / 64 + 3 words.  Ends with a barrier.
 template <int NT>
-__device__ __forceinline__ uint32_t find_bin(uint32_t* hist, uint32_t* red, uint32_t need, uint32_t most,
-                                             int& end) {
+__device__ __forceinline__ uint32_t find_bin(uint32_t* hist, uint32_t* red, uint32_t need, int& end,
+                                             int& cnt) {
   constexpr int NW = NT / WAVE, BPT = NBINS / NT;   // bins per thread
   const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
   static_assert(BPT == 4 || BPT == 2 || BPT == 1, "one vector of bins per thread");
@@ -271,30 +301,50 @@ __device__ __forceinline__ uint32_t find_bin(uint32_t* hist, uint32_t* red, uint
     start[i] = at;
     if (at < need && need <= at + h[i]) {
       red[NW] = at + h[i];
-      red[NW + 1] = h[i] > most ? ~0u : uint32_t(BPT * tid + i);
+      red[NW + 1] = uint32_t(BPT * tid + i);
+      red[NW + 2] = h[i];
     }
     at += h[i];
   }
   reinterpret_cast<bins_t*>(hist)[tid] = start;
   __syncthreads();
   end = int(red[NW]);
+  cnt = int(red[NW + 2]);
   return red[NW + 1];
 }
-template <int NT, int PER, class Key, class Row>
+template <int NT, int PER, bool NARROW, class Key, class Row>
 __device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, uint32_t kmin,
                                               uint32_t kmax, int kk, uint32_t* hist, uint32_t* red,
-                                              uint64_t* sorted, int32_t* oi, float* os) {
-  const KeyBins bin(kmin, kmax);
+                                              uint64_t* sorted, int32_t* oi, float* os, uint32_t& tlo,
+                                              uint32_t& thi) {
+  kmin = max(kmin, 1u);
+  kmax = max(kmax, kmin);
+  KeyBins bin(kmin, kmax);
+  uint32_t last;
+  int total, cnt, was = 2 * NT * PER;
+  while (true) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (key(e) >= kmin) count_in_bin(hist, bin(key(e)));
+    __syncthreads();
+    last = find_bin<NT>(hist, red, uint32_t(kk), total, cnt);
+    tlo = 0u;
+    thi = ~0u;
+    if (last == ~0u) return false;
+    tlo = bin.bottom(last, kmin);
+    thi = bin.top(last);
+    const KeyBins finer(tlo, kmax);
+    if (!NARROW || cnt <= BIN_FEW || finer.shift >= bin.shift || (cnt <= BIN_MOST && 2 * cnt > was)) break;
+    was = cnt;
+    kmin = tlo;
+    bin = finer;
+    for (int b = threadIdx.x; b < NBINS; b += NT) hist[b] = 0u;
+    __syncthreads();
+  }
+  if (cnt > BIN_MOST) return false;
 #pragma unroll
   for (int e = 0; e < PER; ++e)
-    if (key(e)) atomicAdd(&hist[bin(key(e))], 1u);
-  __syncthreads();
-  int total;
-  const uint32_t last = find_bin<NT>(hist, red, uint32_t(kk), BIN_MOST, total);
-  if (last == ~0u) return false;
-#pragma unroll
-  for (int e = 0; e < PER; ++e)
-    if (key(e)) {
+    if (key(e) >= kmin) {
       const uint32_t b = bin(key(e));
       if (b <= last) sorted[atomicAdd(&hist[b], 1u)] = sel_value(key(e), row(e));
     }
@@ -303,8 +353,11 @@ __device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, ui
     const uint64_t me = sorted[i];
     const uint32_t b = bin(sel_key(me));
     const int s0 = b ? int(hist[b - 1]) : 0, s1 = int(hist[b]);
-    int rank = s0;
-    for (int j = s0; j < s1; ++j) rank += sorted[j] > me ? 1 : 0;
+    int rank = s0, j = s0;
+    for (; j + 4 <= s1; j += 4)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) rank += sorted[j + u] > me ? 1 : 0;
+    for (; j < s1; ++j) rank += sorted[j] > me ? 1 : 0;
     if (rank < kk) {
       oi[rank] = sel_row(me);
       os[rank] = key_score(sel_key(me));

@@ -742,9 +742,10 @@ __global__ __launch_bounds__(FT_THREADS) void fsel_select(FusedArgs A, int32_t* 
     }
   block_min_max<FT_THREADS>(lo, hi, bred);
   __syncthreads();   // bred is reused
-  if (place_by_bins<FT_THREADS, PER>([&](int e) { return sel_key(v[e]); },
-                                     [&](int e) { return sel_row(v[e]); }, lo, hi, kk, hist, bred,
-                                     vals, oi, os))
+  uint32_t tlo, thi;
+  if (place_by_bins<FT_THREADS, PER, false>([&](int e) { return sel_key(v[e]); },
+                                            [&](int e) { return sel_row(v[e]); }, lo, hi, kk, hist,
+                                            bred, vals, oi, os, tlo, thi))
     return;
   uint64_t* sel = vals + A.cap;   // [k]
 #pragma unroll

@@ -211,8 +211,8 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
   for (int q = 0; q < GROUPS; ++q)
     if (gm[q]) atomicAdd(&hist[gbin(gm[q])], 1u);
   __syncthreads();
-  int end;
-  const uint32_t last = find_bin<NT>(hist, red, uint32_t(kk), ~0u, end);
+  int end, cnt;
+  const uint32_t last = find_bin<NT>(hist, red, uint32_t(kk), end, cnt);
   // kk estimates reach the smallest key of that bin (min(L, GROUPS x NT) >= kk groups
   // have a row), so the kk-th exact key is at most SLACK below it, and the estimates of
   // the kk best rows 2 SLACK
@@ -256,8 +256,9 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
     }
     const uint32_t kmin = least > SLACK ? least - SLACK : 1u;
     const uint32_t kmax = hi < ~0u - SLACK ? hi + SLACK : ~0u;
-    placed = place_by_bins<NT, LIST / NT>([&](int e) { return key[e]; }, [&](int e) { return row[e]; },
-                                          kmin, kmax, kk, hist, red, sorted, oi, os);
+    uint32_t tlo, thi;
+    placed = place_by_bins<NT, LIST / NT, true>([&](int e) { return key[e]; }, [&](int e) { return row[e]; },
+                                                kmin, kmax, kk, hist, red, sorted, oi, os, tlo, thi);
   }
   if (!placed) {
     uint32_t key[RPT];

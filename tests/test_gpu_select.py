@@ -324,3 +324,51 @@ def test_resident_equals_the_general_search(dtype, d, L):
         assert torch.all(s1[:7][hit] == 0)
         if k >= L:
             assert torch.all(hit.any(1))
+
+
+def ranged_inputs(dist, L, N, d, dtype, seed):
+    """One request of L rows whose score against candidate 0 is the value drawn from `dist`
+    (exact in fp32: two columns of at most 17 bits together), against the others that value
+    times a power of two and a sign."""
+    rng = np.random.default_rng(seed)
+    a = {"both_signs": rng.normal(size=L), "negative": -1 - rng.random(L), "narrow": 1 + rng.random(L) / 128,
+         "outlier": rng.normal(size=L), "octaves": rng.normal(size=L),
+         "two_values": np.where(rng.random(L) < 0.3, 3.0, -2.0)}[dist]
+    hi = np.round(a * 16) / 16
+    lo = np.round(np.clip(a - hi, -1 / 32, 1 / 32) * 2 ** 13) / 2 ** 13
+    if dist == "outlier":
+        hi[L // 2], lo[L // 2] = 2.0 ** 28, 0
+        hi[L // 3], lo[L // 3] = -2.0 ** 28, 0
+    elif dist == "octaves":
+        hi, lo = np.sign(a) * 2.0 ** rng.integers(-20, 20, L), np.zeros(L)
+    elif dist == "two_values":
+        lo[:] = 0
+    w = synth.scaled(synth.SINGLE, R=1, d=d, dtype=dtype, N=N)
+    emb = np.zeros((L, d), np.float32)
+    emb[:, 0], emb[:, 1] = hi, lo
+    cand = np.zeros((N, d), np.float32)
+    cand[:, :2] = (np.where(np.arange(N) % 3 == 2, -1, 1) * 2.0 ** (np.arange(N) % 7 - 3 * (np.arange(N) > 0)))[:, None]
+    cand[0, :2] = 1
+    seq = synth.SeqBatch(emb=emb, act=rng.integers(0, 8, L).astype(np.uint8),
+                         time=np.sort(rng.integers(0, 64, L)).astype(np.uint8), offset=np.zeros(1, np.int64),
+                         length=np.array([L], np.int32))
+    return synth.Inputs(w=w, seq=seq, cand=cand, cand_offset=np.array([0, N], np.int64))
+
+
+@pytest.mark.parametrize("dist", ["both_signs", "negative", "narrow", "outlier", "octaves", "two_values"])
+@pytest.mark.parametrize("dtype,d,L,N", [
+    ("bf16", 16, 900, 3), ("bf16", 16, 2000, 4), ("bf16", 16, 2000, 600), ("bf16", 16, 4096, 5),
+    ("bf16", 16, 4000, 600), ("f32", 16, 3000, 4),                     # score rows in memory
+    ("bf16", 32, 900, 3), ("bf16", 32, 4000, 5), ("bf16", 32, 8192, 4),   # one launch
+    ("bf16", 48, 9000, 4)])                                            # scores on chip
+def test_score_ranges(dist, dtype, d, L, N):
+    """Placement by bins over ranges of scores that one set of equal bins does not resolve:
+    both signs (four bins to a factor of two), one value far out on either side, 40 powers of
+    two, two values; and narrow ones.  k from one row to nearly every row."""
+    print(f"score ranges {dist} {dtype} d={d} L={L} N={N}", flush=True)
+    inp = ranged_inputs(dist, L, N, d, dtype, seed=L + N)
+    ids = np.arange(N) if N <= 8 else np.unique(np.r_[0:8, np.arange(0, N, 97), N - 1])
+    for k in sorted({1, 64, 256, 257, min(L - 1, 1000)}):
+        idx, score = run_select(inp, k)
+        ref_i, ref_s = oracle_select(inp, k, ids=ids)
+        assert_select_equal(idx, score, ref_i, ref_s, ids=ids)
