@@ -11,7 +11,10 @@
 // are binned, and the bin that holds the k-th largest of them bounds the k-th key from
 // below, closely (k = 256 of 16384 rows: about 300 rows reach it).  The rows that reach
 // it get their exact score and are placed by bins.  Where a bin or the list overflows
-// (many equal scores), the k-th key is found bit by bit.
+// (many equal scores), the k-th key is found bit by bit below the bits that are settled
+// and the equal rows go straight to their places (2000 int8 rows of d 32, a third or all of
+// one score, 256 candidates: 9.9 and 8.2 us; 27 and 30 with all 32 bits searched and the
+// selected rows counted; 16.5 by the launches that this kernel takes the place of).
 //
 // What bounds it: launch, first loads and selection are about 10 us; each 1024 rows add
 // 0.5 to 1 us: every workgroup reads all rows from L2 and turns codes into bf16.
@@ -53,63 +56,97 @@ __device__ __forceinline__ bf16x8 codes(uint32_t x, uint32_t y) {
   return as_bf16x8(make_uint4(p[0], p[1], p[2], p[3]));
 }
 
-// The kk best of the workgroup's keys (key[j]: row j NT + thread, 0: none), found bit by
-// bit: every key above the kk-th, then the lowest rows equal to it.  sel: kk values.
+// The kk best of the workgroup's keys (key[j]: row j NT + thread, 0: none), the kk-th of
+// which lies in [tlo, thi] and is found bit by bit below the bits these have in common:
+// every key above it, placed by counting, then the lowest rows equal to it, in row order.
+// cnt: RPT x NT / 64 words, red: 2 x NT / 64; sel: kk values.
 template <int NT, int RPT>
-__device__ __noinline__ void place_by_bits(const uint32_t* key, int kk, uint32_t* red, uint64_t* sel,
-                                           int32_t* oi, float* os) {
+__device__ __forceinline__ void place_by_bits(const uint32_t (&key)[RPT], int kk, uint32_t tlo,
+                                              uint32_t thi, uint32_t* cnt, uint32_t* red,
+                                              uint32_t* above, uint64_t* sel, int32_t* oi, float* os) {
   constexpr int NW = NT / WAVE;
   const int tid = threadIdx.x, lane = tid % WAVE, wid = tid / WAVE;
-  auto total = [&](int c) {   // over the workgroup, of a wave-uniform count
-    __syncthreads();
-    if (lane == 0) red[wid] = uint32_t(c);
-    __syncthreads();
-    int t = 0;
-    for (int w = 0; w < NW; ++w) t += int(red[w]);
-    return t;
-  };
-  uint32_t t = 0;
-  for (int b = 31; b >= 0; --b) {
+  const int top = tlo == thi ? -1 : 31 - __builtin_clz(tlo ^ thi);
+  uint32_t t = top < 0 ? tlo : top == 31 ? 0u : tlo & ~((2u << top) - 1u);
+  __syncthreads();   // cnt, red, sel, above: nothing of them is read any more
+  if (tid == 0) *above = 0u;
+  for (int b = top; b >= 0; --b) {
     const uint32_t probe = t | (1u << b);
     int c = 0;
+#pragma unroll
     for (int j = 0; j < RPT; ++j) c += __popcll(__builtin_amdgcn_ballot_w64(key[j] >= probe));
-    if (total(c) >= kk) t = probe;
+    uint32_t* half = red + (b & 1) * NW;   // (the other half may still be read)
+    if (lane == 0) half[wid] = uint32_t(c);
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) all += int(half[w]);
+    if (all >= kk) t = probe;
   }
-  int above = 0;   // keys above t, in any order; then those equal to it, in row order
-  for (int pass = 0; pass < 2; ++pass)
-    for (int j = 0; j < RPT; ++j) {
-      const bool in = pass ? key[j] == t : key[j] > t;
-      const uint64_t m = __builtin_amdgcn_ballot_w64(in);
-      __syncthreads();
-      if (lane == 0) red[wid] = uint32_t(__popcll(m));
-      __syncthreads();
-      int before = above, all = 0;
-      for (int w = 0; w < NW; ++w) {
-        before += w < wid ? int(red[w]) : 0;
-        all += int(red[w]);
-      }
-      const int pos = before + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0)));
-      if (in && pos < kk) sel[pos] = sel_value(key[j], j * NT + tid);
-      above += all;
+  // rows are ordered by (j, wave, lane): the equal keys are counted per j and wave
+  uint64_t eq[RPT];
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    eq[j] = __builtin_amdgcn_ballot_w64(key[j] == t);
+    if (lane == 0) cnt[j * NW + wid] = uint32_t(__popcll(eq[j]));
+  }
+  __syncthreads();   // (*above is zero as well)
+#pragma unroll
+  for (int j = 0; j < RPT; ++j)
+    if (key[j] > t) sel[atomicAdd(above, 1u)] = sel_value(key[j], j * NT + tid);
+  uint32_t before[RPT];   // equal keys before the wave's of j: one count per lane
+  {
+    constexpr int N = RPT * NW, PER = (N + WAVE - 1) / WAVE;
+    uint32_t v[PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      v[i] = PER * lane + i < N ? cnt[PER * lane + i] : 0u;
+      sum += v[i];
     }
+    uint32_t at = wave_incl_sum(sum) - sum;
+    uint32_t ex[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      ex[i] = at;
+      at += v[i];
+    }
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+      const int e = j * NW + wid;   // wave-uniform
+      before[j] = 0;
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (e % PER == i) before[j] = uint32_t(__builtin_amdgcn_readlane(int(ex[i]), e / PER));
+    }
+  }
   __syncthreads();
-  place_by_rank<NT>(sel, kk, oi, os);
+  const int gt = int(*above);
+  const float score = key_score(t);
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    const int pos = gt + int(before[j] + __builtin_amdgcn_mbcnt_hi(uint32_t(eq[j] >> 32),
+                                                                   __builtin_amdgcn_mbcnt_lo(uint32_t(eq[j]), 0)));
+    if (key[j] == t && pos < kk) {
+      oi[pos] = j * NT + tid;
+      os[pos] = score;
+    }
+  }
+  place_by_rank<NT>(sel, gt, oi, os);
 }
 
-// A row's score from its product (and, for codes, its sum of squares): exact, and the
-// estimate through the hardware reciprocal square root.  The two have the same sign and
-// keys at most SLACK apart (relative error below 2^-21); an all-zero row scores 0 whatever
-// its product (0 x inf), and of the other rows a product that is not a number is its own
-// score in both.
+// A row's score from its product (and, for codes, its sum of squares ss > 0): exact, and
+// the estimate through the hardware reciprocal square root.  The two have the same sign and
+// keys at most SLACK apart (relative error below 2^-21); a product that is not a number is
+// its own score in both.  An all-zero row scores 0 whatever the candidate (its product may
+// be 0 x inf): it enters as product 0 and ss 1.
 constexpr uint32_t SLACK = 64;
 template <bool I8>
 __device__ __forceinline__ uint32_t exact_key(float dot, float ss) {
-  return score_key(I8 && (dot == dot || !(ss > 0.f)) ? i8_score(dot, ss) : dot);
+  return score_key(I8 && dot == dot ? i8_score(dot, ss) : dot);
 }
 template <bool I8>
 __device__ __forceinline__ uint32_t estimate_key(float dot, float ss) {
-  const float est = ss > 0.f ? dot * __builtin_amdgcn_rsqf(ss) : 0.f;
-  return score_key(I8 && (dot == dot || !(ss > 0.f)) ? est : dot);
+  return score_key(I8 ? dot * __builtin_amdgcn_rsqf(ss) : dot);
 }
 
 // NT threads, RPT rows per thread (the rows fit NT x RPT), d = 16 KB.
@@ -157,7 +194,8 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
   uint32_t gm[GROUPS] = {};   // the largest estimates of rows j modulo GROUPS
 #pragma unroll
   for (int j = 0; j < RPT; ++j) {
-    ss[j] = 0.f;
+    ss[j] = 1.f;
+    bool norm = true;
     f32x16 acc[2] = {f32x16{}, f32x16{}};
     uint32_t x[ROW / 4];
 #pragma unroll
@@ -173,7 +211,8 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
       int sq = 0;
 #pragma unroll
       for (int i = 0; i < ROW / 4; ++i) sq = __builtin_amdgcn_sdot4(int(x[i]), int(x[i]), sq, false);
-      ss[j] = float(sq);
+      ss[j] = float(max(sq, 1));
+      norm = sq > 0;
     }
     // the lower lanes hold tile 0's rows, the upper tile 1's: words of k and k + 8
     // change places across the halves and become the two tiles' operands
@@ -195,7 +234,7 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
         acc[1] = mfma32(cf[kb], as_bf16x8(make_uint4(t1[0], t1[1], t1[2], t1[3])), acc[1]);
       }
     }
-    dot[j] = hf ? acc[1][0] : acc[0][0];
+    dot[j] = norm ? (hf ? acc[1][0] : acc[0][0]) : 0.f;
     gm[j % GROUPS] = max(gm[j % GROUPS], NT * j + tid < L ? estimate_key<I8>(dot[j], ss[j]) : 0u);
   }
   uint32_t lo = ~0u, hi = 0u;
@@ -209,7 +248,7 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
   const KeyBins gbin(lo, hi);
 #pragma unroll
   for (int q = 0; q < GROUPS; ++q)
-    if (gm[q]) atomicAdd(&hist[gbin(gm[q])], 1u);
+    if (gm[q]) count_in_bin(hist, gbin(gm[q]));
   __syncthreads();
   int end, cnt;
   const uint32_t last = find_bin<NT>(hist, red, uint32_t(kk), end, cnt);
@@ -240,6 +279,9 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
     }
   __syncthreads();
   const uint32_t total = listed;
+  const uint32_t kmin = least > SLACK ? least - SLACK : 1u;   // of the kk best rows' exact keys
+  const uint32_t kmax = hi < ~0u - SLACK ? hi + SLACK : ~0u;
+  uint32_t tlo = kmin, thi = kmax;
   bool placed = false;
   if (total <= uint32_t(LIST)) {
     uint32_t key[LIST / NT];
@@ -254,9 +296,6 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
         row[e] = list_row[i];
       }
     }
-    const uint32_t kmin = least > SLACK ? least - SLACK : 1u;
-    const uint32_t kmax = hi < ~0u - SLACK ? hi + SLACK : ~0u;
-    uint32_t tlo, thi;
     placed = place_by_bins<NT, LIST / NT, true>([&](int e) { return key[e]; }, [&](int e) { return row[e]; },
                                                 kmin, kmax, kk, hist, red, sorted, oi, os, tlo, thi);
   }
@@ -265,7 +304,7 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
 #pragma unroll
     for (int j = 0; j < RPT; ++j)
       key[j] = NT * j + tid < L ? max(exact_key<I8>(dot[j], ss[j]), 1u) : 0u;
-    place_by_bits<NT, RPT>(key, kk, red, sorted, oi, os);
+    place_by_bits<NT, RPT>(key, kk, tlo, thi, hist, red, &listed, sorted, oi, os);
   }
 }
 
