@@ -55,7 +55,16 @@ constexpr int DM = 64;          // d_model
 constexpr int TT = 16;          // tokens per wave
 constexpr int MAX_NW = 12;      // waves per workgroup at most
 constexpr int MAX_LAYERS = 4;
-constexpr int MAX_DK = 8;       // token width d <= 256: at most 8 k-steps of 32 (kernels for 1, 2, 8)
+constexpr int MAX_DK = 8;       // token width d <= 256: at most 8 k-steps of 32 (kernels for 1, 2, 4, 8)
+// From so many k-steps on, the waves share the candidates' projections (W_in's candidate
+// half from memory, once a candidate) instead of each taking the product for its tile.  us,
+// each product of its own : shared; one layer, FFN 32, candidates x positions:
+//   d     2000 x 8     256 x 64    256 x 192   2000 x 192  300 x 1000
+//   128   12.8 : 15.9              16.6 : 15.7  102 : 99    246 : 214
+//   256   27.0 : 22.0  14.2 : 13.5 48.0 : 20.3  336 : 129   572 : 284  (no room for either half)
+// At d 96 and 128 many short candidates would pay for the rest.
+constexpr int COOP_DK = 5;
+constexpr int GROUP_NW = 8;     // waves of candidates side by side at most
 constexpr int FRAG = 1024;      // bytes of a 16 x 32 operand fragment
 constexpr int RLD = DM + 8;           // row stride (bf16) of the packed matrices over d_model
 constexpr int TABLD = DM * 2 + 16;    // bytes between the side tables' rows (their bank conflicts)
@@ -124,11 +133,11 @@ struct Args {
   float* out;                // [total, 2 DM]
   LayerW pk[MAX_LAYERS];     // offsets in the packed weights
   int packed_bytes;
-  // LDS layout (bytes): W_in (both halves; win < 0: no room, read from memory), the
-  // side tables, b_in and the layers' vectors, the layers' matrices, W_pool (pool_w < 0:
-  // no room), K / V^T (then the pooled maxima)
+  // LDS layout (bytes): the side tables, b_in and the layers' vectors, the layers'
+  // matrices, the candidates' projections (where shared), W_in's token half and candidate
+  // half and W_pool (each < 0: no room, read from memory), K / V^T (then the pooled maxima)
   LayerW lw[MAX_LAYERS];
-  int win, tab, bias, pool_w, kv;
+  int tab, bias, cvec, win_t, win_c, pool_w, kv;
   int tab16;                 // the side tables are 16-byte aligned
   int unmasked;
 };
@@ -159,17 +168,21 @@ __host__ inline void plan_packed(Args& a) {
   take(DM * (a.d + 8) * 2);
   a.packed_bytes = off;
 }
-// The LDS layout up to K / V^T (`whole`: with W_in and W_pool); returns its size.
+// The LDS layout up to K / V^T; returns its size.  `room`: the bytes it may take.  W_in's
+// token half, its candidate half and W_pool are held while there is room, in this order
+// (every wave reads each of them once for every tile: with all three or none, 2000
+// candidates of 192 positions took 171 us at two layers and d 64, and 335 at one and d
+// 256; now 137 and 129).
 // Matrices as fragments (row tile f, k-block kb) at (f * nkb + kb) * FRAG; W_in and
 // W_2, whose k-blocks are taken one by one, at (kb * 4 + f) * FRAG.
-__host__ inline int plan_lds(Args& a, bool whole) {
+__host__ inline int plan_lds(Args& a, int room) {
   int off = 0;
   auto take = [&](int bytes) {
     const int at = off;
     off += (bytes + 15) / 16 * 16;
     return at;
   };
-  a.win = whole ? take(2 * a.d * DM * 2) : -1;
+  const bool coop = a.d / 32 >= COOP_DK;
   a.tab = take(TAB_BYTES);
   a.bias = off;
   off += DM * 4;
@@ -181,7 +194,11 @@ __host__ inline int plan_lds(Args& a, bool whole) {
     a.lw[l].w1 = take(a.ffn * DM * 2);
     a.lw[l].w2 = take(DM * a.ffn * 2);
   }
-  a.pool_w = whole ? take(DM * DM * 2) : -1;
+  a.cvec = coop ? take(GROUP_NW * DM * 4) : -1;
+  auto held = [&](int bytes) { return off + bytes <= room ? take(bytes) : -1; };
+  a.win_t = held(a.d * DM * 2);
+  a.win_c = coop ? -1 : held(a.d * DM * 2);
+  a.pool_w = held(DM * DM * 2);
   a.kv = off;
   return off;
 }
@@ -230,12 +247,12 @@ __device__ __forceinline__ void dma_layers(const Args& A, uint8_t* smem, int fro
                                            int n) {
   const int ffn = A.ffn;
   const bool p = A.packed != nullptr;
-  if (from == 0 && A.win >= 0) {
-    const int half = A.d / 8 * FRAG;   // the token half's fragments, then the candidate's
+  if (from == 0) {
     const uint8_t* w = reinterpret_cast<const uint8_t*>(A.W_in);
-    dma_matrix(smem + A.win, p ? A.packed + A.packed_bytes - DM * (A.d + 8) * 2 : w, p ? 0 : 4 * A.d, 4,
-               A.d / 32, true, false, i, n);
-    dma_matrix(smem + A.win + half, w + 2 * A.d, 4 * A.d, 4, A.d / 32, true, false, i, n);
+    if (A.win_t >= 0)
+      dma_matrix(smem + A.win_t, p ? A.packed + A.packed_bytes - DM * (A.d + 8) * 2 : w, p ? 0 : 4 * A.d,
+                 4, A.d / 32, true, false, i, n);
+    if (A.win_c >= 0) dma_matrix(smem + A.win_c, w + 2 * A.d, 4 * A.d, 4, A.d / 32, true, false, i, n);
   }
   for (int l = from; l < to; ++l) {
     const tav2_layer& L = A.layers[l];
@@ -305,17 +322,24 @@ __device__ __forceinline__ void copy_tables(const Args& A, uint8_t* smem) {
     *reinterpret_cast<uint4*>(smem + A.tab + e * 16) = make_uint4(lo.x, lo.y, hi.x, hi.y);
   }
 }
-// Four fragments (row tiles f) of k-block kb of W_in, or of row tile pair h of W_pool
-// (two tiles x two k-blocks): from LDS, or from the matrix.
-__device__ __forceinline__ void win_frags(bf16x8 (&wf)[4], const Args& A, const uint8_t* smem, int kb) {
+// Fragment (row tile f) of k-block kb of W_in from the matrix (kb >= d / 32: its candidate
+// half).
+__device__ __forceinline__ bf16x8 win_frag(const Args& A, int kb, int f) {
   const int lane = otid() % WAVE;
-  if (A.win >= 0) {
+  return frag(A.W_in + (feature_row(f, lane % 16) * 2 * A.d + 32 * kb + 8 * (lane / 16)));
+}
+// Four fragments (row tiles f) of k-block kb of the half of W_in that LDS holds at `at`
+// (matrix k-block kb0 + kb), or of row tile pair h of W_pool (two tiles x two k-blocks): from
+// LDS, or (at < 0) from the matrix.
+__device__ __forceinline__ void win_frags(bf16x8 (&wf)[4], const Args& A, const uint8_t* smem, int at,
+                                          int kb0, int kb) {
+  const int lane = otid() % WAVE;
+  if (at >= 0) {
 #pragma unroll
-    for (int f = 0; f < 4; ++f) wf[f] = frag(smem + A.win + (kb * 4 + f) * FRAG + lane * 16);
+    for (int f = 0; f < 4; ++f) wf[f] = frag(smem + at + (kb * 4 + f) * FRAG + lane * 16);
   } else {
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-      wf[f] = frag(A.W_in + (feature_row(f, lane % 16) * 2 * A.d + 32 * kb + 8 * (lane / 16)));
+    for (int f = 0; f < 4; ++f) wf[f] = win_frag(A, kb0 + kb, f);
   }
 }
 __device__ __forceinline__ void pool_frags(bf16x8 (&wf)[4], const Args& A, const uint8_t* smem, int h) {
@@ -415,14 +439,33 @@ __device__ __forceinline__ void load_token(TokLoad<NK>& L, int64_t n, int p, int
     }
   }
 }
+// The candidate's half of Eq. 4, W_in[:, d:] c, into cv[feature]: the features of row tile
+// f (every column of the product is the same).
+template <int NK>
+__device__ __forceinline__ void project_candidate(float* cv, const bf16_t* cand, const Args& A, int nk,
+                                                  int f) {
+  const int lane = otid() % WAVE, g = lane / 16;
+  bf16x8 wf[NK], cf[NK];
+#pragma unroll
+  for (int k = 0; k < NK; ++k)
+    if (k < nk) {
+      wf[k] = win_frag(A, nk + k, f);
+      cf[k] = frag(cand + 32 * k + 8 * g);
+    }
+  f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < NK; ++k)
+    if (k < nk) a = mma(wf[k], cf[k], a);
+  if (lane % 16 == 0) *reinterpret_cast<f32x4*>(cv + feat4(f, g)) = a;
+}
 // x = X0^T of the wave's 16 tokens (Eq. 4): W_in [e ; c] + b_in + side tables.  The
 // candidate (cf) enters as a product with the same column for every token (for
 // int8 codes after the token product is scaled by the 0.65 / 127 of their
-// quantisation, Sec. 3.2.1).
+// quantisation, Sec. 3.2.1), or as its projection cv.
 template <int NK>
 __device__ __forceinline__ void encode_input(f32x4 (&x)[4], const TokLoad<NK>& tl,
-                                             const bf16x8 (&cf)[NK], const Args& A,
-                                             const uint8_t* smem, int nk) {
+                                             const bf16x8 (&cf)[NK], const float* cv,
+                                             const Args& A, const uint8_t* smem, int nk) {
   const int g = otid() % WAVE / 16;
 #pragma unroll
   for (int f = 0; f < 4; ++f) x[f] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -430,7 +473,7 @@ __device__ __forceinline__ void encode_input(f32x4 (&x)[4], const TokLoad<NK>& t
   for (int k = 0; k < NK; ++k)
     if (k < nk) {
       bf16x8 wf[4];
-      win_frags(wf, A, smem, k);
+      win_frags(wf, A, smem, A.win_t, 0, k);
       if (NK > 2) fence();
 #pragma unroll
       for (int f = 0; f < 4; ++f) x[f] = mma(wf[f], tl.e[k], x[f]);
@@ -439,15 +482,20 @@ __device__ __forceinline__ void encode_input(f32x4 (&x)[4], const TokLoad<NK>& t
 #pragma unroll
     for (int f = 0; f < 4; ++f) x[f] *= 0.65f / 127.f;
   }
+  if constexpr (NK >= COOP_DK) {
 #pragma unroll
-  for (int k = 0; k < NK; ++k)
-    if (k < nk) {
-      bf16x8 wf[4];
-      win_frags(wf, A, smem, nk + k);
-      if (NK > 2) fence();
+    for (int f = 0; f < 4; ++f) x[f] += *reinterpret_cast<const f32x4*>(cv + feat4(f, g));
+  } else {
 #pragma unroll
-      for (int f = 0; f < 4; ++f) x[f] = mma(wf[f], cf[k], x[f]);
-    }
+    for (int k = 0; k < NK; ++k)
+      if (k < nk) {
+        bf16x8 wf[4];
+        win_frags(wf, A, smem, A.win_c, nk, k);
+        if (NK > 2) fence();
+#pragma unroll
+        for (int f = 0; f < 4; ++f) x[f] = mma(wf[f], cf[k], x[f]);
+      }
+  }
   const float* bias = reinterpret_cast<const float*>(smem + A.bias);
   const uint8_t* ta = smem + A.tab + tl.act * TABLD;
   const uint8_t* tt = smem + A.tab + (8 + tl.time) * TABLD;
@@ -625,11 +673,17 @@ __global__ __launch_bounds__(NW* WAVE) void encoder_small_kernel(Args A) {
       {
         TokLoad<NK> tl;
         bf16x8 cf[NK];
+        float* cv = reinterpret_cast<float*>(smem + A.cvec);
+        if (NK >= COOP_DK && blk == 0)   // every wave takes its share of the row tiles
+          for (int t = w; t < 4 * A.groups && n0 + t / 4 < A.total; t += int(blockDim.x) / WAVE)
+            project_candidate<NK>(cv + t / 4 * DM, A.cand + (n0 + t / 4) * A.d, oargs(), nk, t % 4);
         if (live) {
-          const bf16_t* cr = A.cand + n * A.d + 8 * g;
+          if (NK < COOP_DK) {
+            const bf16_t* cr = A.cand + n * A.d + 8 * g;
 #pragma unroll
-          for (int k = 0; k < NK; ++k)
-            if (k < nk) cf[k] = frag(cr + 32 * k);
+            for (int k = 0; k < NK; ++k)
+              if (k < nk) cf[k] = frag(cr + 32 * k);
+          }
           load_token(tl, n, p, Tv, oargs(), nk);
         }
         if (loaded == 0) {
@@ -637,8 +691,10 @@ __global__ __launch_bounds__(NW* WAVE) void encoder_small_kernel(Args A) {
           wait_vm_all();
           __syncthreads();
           loaded = A.n_layers > 1 ? 1 : 3;
+        } else if (NK >= COOP_DK && blk == 0) {
+          __syncthreads();   // cv is complete (read last before the previous candidate's layers)
         }
-        if (live) encode_input(x, tl, cf, oargs(), smem, nk);
+        if (live) encode_input(x, tl, cf, cv + grp * DM, oargs(), smem, nk);
       }
       for (int li = 0; li < A.n_layers; ++li) {
         const int lane = otid() % WAVE, c16 = lane % 16, g = lane / 16;
@@ -917,7 +973,6 @@ __global__ __launch_bounds__(256) void small_pack_kernel(PackArgs P) {
 namespace {
 constexpr size_t SM_CACHE_BUDGET = size_t(1) << 30;   // K/V cache bytes at most
 constexpr int SM_LDS_MAX = 160 * 1024;
-constexpr int SM_GROUP_NW = 8;   // waves of candidates side by side at most
 
 sm::Args small_args(const tav2_weights& w, int d) {
   sm::Args a{};
@@ -938,7 +993,7 @@ struct SmallPlan {
 };
 int small_pairs(const sm::Args& a) {   // pairs next to what LDS has to hold
   sm::Args b = a;
-  return (SM_LDS_MAX - sm::plan_lds(b, false)) / sm::PAIR;
+  return (SM_LDS_MAX - sm::plan_lds(b, 0)) / sm::PAIR;
 }
 SmallPlan small_plan(int T, const sm::Args& a) {
   const int avail = small_pairs(a);
@@ -963,7 +1018,7 @@ int device_cus() {
 // workgroup, at most what the LDS and 16 waves hold.
 int small_groups(int64_t total, const SmallPlan& p, const sm::Args& a, int cus) {
   if (p.blocks > 1) return 1;
-  const int most = std::max(1, std::min(SM_GROUP_NW / p.nwc, small_pairs(a) / p.npair));
+  const int most = std::max(1, std::min(sm::GROUP_NW / p.nwc, small_pairs(a) / p.npair));
   const int64_t want = cdiv(total, int64_t(cus));
   return int(std::max<int64_t>(1, std::min<int64_t>(want, most)));
 }
@@ -1084,25 +1139,25 @@ hipError_t launch_encode_small(const TokenSource& src, const void* cand_emb, int
   a.groups = small_groups(total, p, a, cus);
   a.cache_pairs = (p.blocks - 1) * p.npair;
   a.cache = p.blocks > 1 ? static_cast<uint8_t*>(ws) : nullptr;
-  // W_in and W_pool where the LDS has room for them
   const int kvb = a.groups * a.npair * sm::PAIR;
-  if (sm::plan_lds(a, true) + kvb > SM_LDS_MAX) sm::plan_lds(a, false);
+  sm::plan_lds(a, SM_LDS_MAX - kvb);
   const int lds = a.kv + kvb;
   const int grid = small_grid(total, src.T, w.n_layers, a.groups, cus);
   const int nk = src.d / 32;
   // (spare waves, up to the 8 or 12 that the kernel is built for, help to load weights)
   const bool multi = p.blocks > 1;
   const int waves = !multi && a.groups * a.nwc <= 8 ? 8 : sm::MAX_NW;
-  const int which = (nk <= 1 ? 0 : nk <= 2 ? 1 : 2) + (a.dh == 64 ? 0 : 3) +
-                    (multi ? 12 : waves == 8 ? 0 : 6);
+  const int which = (nk <= 1 ? 0 : nk <= 2 ? 1 : nk <= 4 ? 2 : 3) + (a.dh == 64 ? 0 : 4) +
+                    (multi ? 16 : waves == 8 ? 0 : 8);
 #define SM_KERNELS(NW, M)                                                                  \
   sm::encoder_small_kernel<1, 64, NW, M>, sm::encoder_small_kernel<2, 64, NW, M>,          \
-      sm::encoder_small_kernel<8, 64, NW, M>, sm::encoder_small_kernel<1, 32, NW, M>,      \
-      sm::encoder_small_kernel<2, 32, NW, M>, sm::encoder_small_kernel<8, 32, NW, M>
-  void (*const kernels[18])(sm::Args) = {SM_KERNELS(8, false), SM_KERNELS(sm::MAX_NW, false),
+      sm::encoder_small_kernel<4, 64, NW, M>, sm::encoder_small_kernel<8, 64, NW, M>,      \
+      sm::encoder_small_kernel<1, 32, NW, M>, sm::encoder_small_kernel<2, 32, NW, M>,      \
+      sm::encoder_small_kernel<4, 32, NW, M>, sm::encoder_small_kernel<8, 32, NW, M>
+  void (*const kernels[24])(sm::Args) = {SM_KERNELS(8, false), SM_KERNELS(sm::MAX_NW, false),
                                          SM_KERNELS(sm::MAX_NW, true)};
 #undef SM_KERNELS
-  static std::atomic<bool> done[64][18] = {};
+  static std::atomic<bool> done[64][24] = {};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;

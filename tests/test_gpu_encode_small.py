@@ -156,11 +156,17 @@ def test_repeated_runs_bitwise_identical():
     (1, 9, {}), (15, 600, {}), (16, 300, dict(n_heads=2)), (17, 520, {}), (33, 300, {}),
     (128, 270, {}), (129, 30, {}), (191, 30, dict(n_heads=2)), (193, 30, {}), (257, 20, {}),
     (385, 12, dict(d=64)), (577, 8, dict(n_layers=1, d_ffn=160)),
-    (200, 20, dict(n_layers=1, d=256)), (100, 20, dict(n_layers=1, d_ffn=96, d=128))])
+    (200, 20, dict(n_layers=1, d=256)), (100, 20, dict(n_layers=1, d_ffn=96, d=128)),
+    # what of W_in and W_pool is held next to 6 key pairs; a candidate's projection shared by
+    # its waves: one to twelve of them, several candidates side by side, several blocks
+    (192, 30, dict(d=64)), (180, 300, dict(n_layers=1, d=96)), (192, 30, dict(n_layers=1, d=256)),
+    (16, 600, dict(n_layers=1, d=256)), (40, 600, dict(n_layers=1, d=160, n_heads=2)),
+    (129, 300, dict(n_layers=1, d=224)), (400, 270, dict(n_layers=1, d=192, n_heads=2)),
+    (300, 9, dict(n_layers=1, d=128))])
 def test_tile_and_block_edges(T_, total, kw):
     """Waves of 16 tokens, pairs of 32 keys, one block of up to 192 positions or several
     of about one size, several short candidates to a workgroup (more than one per CU),
-    and weights that leave no room for W_in and W_pool on chip; packed weights too."""
+    and weights that leave no room for all of W_in and W_pool on chip; packed weights too."""
     print(f"encode_small edges T={T_} total={total} {kw}", flush=True)
     rng = np.random.default_rng(T_)
     edges = [e for e in (0, 1, 15, 16, 17, 31, 32, 33, T_ - 1, T_) if 0 <= e <= T_]
