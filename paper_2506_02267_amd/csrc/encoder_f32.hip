@@ -90,14 +90,18 @@ __device__ __forceinline__ void phase(Ring<DT, PF>& q, f32x4 (&acc)[DT], const f
                                       const Mat& cur, const Mat& next) {
 #pragma unroll
   for (int r = 0; r < DT; ++r) {
-    f32x4 part[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    // past the matrix a row tile is zero (skipped at widths of 100 to 124 only, 66 -> 62 us at
+    // 100: elsewhere the branch costs what it saves, 26.6 -> 28.6 at 64)
+    if (DT < 8 || 16 * r < cur.rows) {   // wave-uniform
+      f32x4 part[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+      for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int f = 0; f < DT; ++f)
-        part[f % 2] = TOK ? mma(x[f][s], q.a[r % PF][f][s], part[f % 2])
-                          : mma(q.a[r % PF][f][s], x[f][s], part[f % 2]);
-    acc[r] += part[0] + part[1];
+        for (int f = 0; f < DT; ++f)
+          part[f % 2] = TOK ? mma(x[f][s], q.a[r % PF][f][s], part[f % 2])
+                            : mma(q.a[r % PF][f][s], x[f][s], part[f % 2]);
+      acc[r] += part[0] + part[1];
+    }
     load_rows<DT>(q.a[r % PF], r + PF < DT ? cur : next, r + PF < DT ? r + PF : r + PF - DT);
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -152,7 +156,10 @@ __device__ __forceinline__ void layer_norm(f32x4 (&x)[DT], const f32x4 (&gain)[D
     for (int i = 0; i < 4; ++i) x[f][i] = x[f][i] * rs * gain[f][i] + off[f][i];
 }
 
-// DT: tiles of 16 features (d_model <= 16 DT); PF: row tiles of weights in flight.
+// DT: tiles of 16 features (d_model <= 16 DT); PF: row tiles of weights in flight.  Every
+// product takes DT x DT tiles, so there is a kernel for each 32 features: us at one
+// position and 16 candidates, with kernels for 64 and 128 only : so (one or two layers)
+//   d_model 8: 32.2 : 14.0   16: 23.3 : 11.8   32: 21.7 : 11.5   68: 65.0 : 45.8   96: 78.5 : 49.6
 template <int DT, int PF>
 __global__ __launch_bounds__(MAX_NW* WAVE) void encode_f32_kernel(Args A) {
   constexpr int DP = 16 * DT, LDK = DP + 4;
@@ -423,20 +430,22 @@ hipError_t launch_encode_f32(const TokenSource& src, const void* cand_emb, int64
   a.unmasked = unmasked ? 1 : 0;
   const int nw = (src.T + f32e::TT - 1) / f32e::TT;
   a.ldv = 16 * nw + 4;
-  const bool narrow = w.d_model <= 64;
-  const int dp = narrow ? 64 : 128;
+  const int which = (w.d_model - 1) / 32;   // 32 (which + 1) features
+  const int dp = 32 * (which + 1);
   const size_t lds = size_t(16 * nw * (dp + 4) + dp * a.ldv + nw * dp) * 4;
   const size_t lds_max = size_t(64 * (128 + 4) + 128 * 68 + 4 * 128) * 4;
-  void (*const kernel)(f32e::Args) = narrow ? f32e::encode_f32_kernel<4, 4> : f32e::encode_f32_kernel<8, 2>;
-  static std::atomic<bool> done[64][2] = {};
+  void (*const kernels[4])(f32e::Args) = {f32e::encode_f32_kernel<2, 2>, f32e::encode_f32_kernel<4, 4>,
+                                          f32e::encode_f32_kernel<6, 2>, f32e::encode_f32_kernel<8, 2>};
+  void (*const kernel)(f32e::Args) = kernels[which];
+  static std::atomic<bool> done[64][4] = {};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64 || !done[dev][narrow].load(std::memory_order_acquire)) {
+  if (dev < 0 || dev >= 64 || !done[dev][which].load(std::memory_order_acquire)) {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_max));
     if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < 64) done[dev][narrow].store(true, std::memory_order_release);
+    if (dev >= 0 && dev < 64) done[dev][which].store(true, std::memory_order_release);
   }
   ProfScope prof("encode_f32", st);
   hipLaunchKernelGGL(kernel, dim3(unsigned(total)), dim3(unsigned(nw * WAVE)), lds, st, a);

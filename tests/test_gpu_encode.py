@@ -252,7 +252,14 @@ def test_packed_weights_equal_per_call_packing(k):
     dict(d=80, d_model=20, n_heads=5, d_ffn=12, n_layers=2, k=16),
     dict(d=16, d_model=60, n_heads=3, d_ffn=68, n_layers=1, k=17),
     dict(d=176, d_model=68, n_heads=1, d_ffn=132, n_layers=1, k=33),
-    dict(d=48, d_model=100, n_heads=5, d_ffn=20, n_layers=2, k=49)])
+    dict(d=48, d_model=100, n_heads=5, d_ffn=20, n_layers=2, k=49),
+    # the kernels of 32, 64, 96 and 128 features, at and just past each width
+    dict(d=64, d_model=32, n_heads=2, d_ffn=36, n_layers=2, k=20),
+    dict(d=32, d_model=36, n_heads=3, d_ffn=64, n_layers=1, k=47),
+    dict(d=32, d_model=64, n_heads=4, d_ffn=60, n_layers=1, k=5),
+    dict(d=112, d_model=96, n_heads=8, d_ffn=100, n_layers=2, k=40),
+    dict(d=16, d_model=116, n_heads=1, d_ffn=128, n_layers=1, k=18),
+    dict(d=144, d_model=128, n_heads=2, d_ffn=140, n_layers=1, k=30)])
 def test_fp32_encoder_tile_edges(shape, flags):
     w = synth.scaled(synth.TINY, R=3, L=None, L_range=(1, 60), N=7, **shape)
     check_workload(w, flags=flags)
