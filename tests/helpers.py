@@ -37,6 +37,19 @@ def assert_select_equal(idx_gpu, score_gpu, idx_ref, score_ref, ids=None):
     assert np.array_equal(sg.view(np.uint32), score_ref.astype(np.float32).view(np.uint32))
 
 
+def launched_sites(call):
+    """The library's launch sites (kernel names) that call() ran, in a set: the path taken."""
+    torch.cuda.synchronize()
+    T.profile_report()
+    T.profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+    finally:
+        T.profile_enable(False)
+    return set(T.profile_report())
+
+
 def max_abs(out_gpu, out_ref, ids=None):
     og = out_gpu.cpu().numpy().astype(np.float64)
     if ids is not None:

@@ -223,10 +223,10 @@ def test_encode_argument_errors(case, status):
 
 
 def test_small_encoder_queries():
-    """d_model 64 (bf16): the packed form is the kernel's LDS image of the weights
-    (per layer: W_qkv, W_o and W_1 in rows of 72 bf16, W_2 in rows of FFN + 8, the
-    eight vectors in fp32; then W_in's token half in rows of d + 8); a workspace of
-    per-workgroup K / V caches past one 64-position block (layers x 2 x T padded
+    """d_model 64 (bf16): the packed form has a slot per matrix and vector (per layer:
+    W_qkv, W_o and W_1 of the size of rows of 72 bf16, W_2 of rows of FFN + 8, the
+    eight vectors in fp32; then W_in's token half of rows of d + 8); a workspace of
+    per-workgroup K / V caches past 64 positions (layers x 2 x T padded
     to 64 x d_model bf16 per workgroup, one workgroup per candidate up to 256);
     the shapes whose weights outgrow the on-chip memory are unsupported."""
     lib = T.load_library()

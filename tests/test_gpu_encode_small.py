@@ -25,8 +25,8 @@ def weights_for(T_, d=32, n_heads=1, d_ffn=32, n_layers=2, has_time=True, seed=N
 
 def ragged_lengths(total, T_, rng):
     """Valid lengths over [0, T_] with the edges of 64-position steps (63, 64, 65,
-    127, 128, 129, ...: the encoder's blocks are 64 positions, its key pairs 32)
-    and the extremes (0, 1, T_) present."""
+    127, 128, 129, ...; among them those of the encoder's tiles of 16 tokens, its pairs of
+    32 keys and its blocks of up to 192 positions) and the extremes (0, 1, T_) present."""
     edges = [0, 1, T_]
     for e in range(64, T_ + 1, 64):
         edges += [e - 1, e, e + 1]
@@ -52,8 +52,8 @@ def run_and_check(tb, W, flags=T.MASK_CAUSAL, ids=None, tol=BF16_TOL):
 
 @pytest.mark.parametrize("T_,total", [(64, 48), (192, 64), (256, 40), (1000, 12), (2048, 8)])
 def test_paper_shape_ragged(T_, total):
-    """d 32, one head, FFN 32, two layers; positions spanning 1 to 32 blocks of
-    64, every block edge among the valid lengths."""
+    """d 32, one head, FFN 32, two layers; one block of up to 192 positions, and up to
+    eleven, every edge of 64 among the valid lengths."""
     print(f"encode_small T={T_} total={total}", flush=True)
     rng = np.random.default_rng(T_)
     tb = synth.make_tokens(total, T_, 32, seed=T_, valid_len=ragged_lengths(total, T_, rng))
@@ -79,8 +79,8 @@ def test_other_shapes(case):
 
 
 def test_many_candidates_persistent_loop():
-    """2,500 candidates at 192 positions: about ten candidates per workgroup, each
-    reusing the workgroup's K/V cache; every 16th candidate and the last checked."""
+    """2,500 candidates at 192 positions: about ten candidates per workgroup, one after the
+    other over the same keys and values in LDS; every 16th candidate and the last checked."""
     total, T_ = 2500, 192
     print(f"encode_small persistent total={total}", flush=True)
     rng = np.random.default_rng(3)
@@ -91,7 +91,7 @@ def test_many_candidates_persistent_loop():
 
 @pytest.mark.parametrize("n_heads", [1, 2])
 def test_unmasked_one_block(n_heads):
-    """TAV2_MASK_NONE within one block of 64: every valid token sees every valid
+    """TAV2_MASK_NONE (up to 64 positions): every valid token sees every valid
     token, padding excluded."""
     print(f"encode_small unmasked heads={n_heads}", flush=True)
     rng = np.random.default_rng(n_heads)
@@ -116,7 +116,7 @@ def test_paper_workload_select_encode():
 
 @pytest.mark.parametrize("kw", [dict(), dict(n_heads=2, d=64)])
 def test_packed_weights_equal_unpacked(kw):
-    """Weights packed once (the kernel's LDS image, loaded by one contiguous copy)
+    """Weights packed once (as operand fragments, copied into LDS as they stand)
     give the outputs of the weights read as given, bit for bit."""
     d = kw.get("d", 32)
     tb = synth.make_tokens(64, 192, d, seed=4, valid_len=np.random.default_rng(4).integers(0, 193, 64))

@@ -18,9 +18,12 @@ CASES = {
     # d_model 256: one encoder block; two blocks (cached keys)
     "single_k64": dict(base=synth.SINGLE, L=3000, N=70, k=64),
     "single_k256": dict(base=synth.SINGLE, L=3000, N=70, k=256),
-    # the paper's encoder shape (d_model 64) behind the fused search (rows > 4096),
-    # with a real-time tail: three 64-position blocks
+    # the paper's encoder shape (d_model 64) behind the search in one launch, with a
+    # real-time tail: one block of 192 positions
     "paper": dict(base=synth.PAPER, L=6000, N=40),
+    # behind the search with scores on chip (rows > 4096, more than 256 candidates): two
+    # blocks (cached keys)
+    "paper_chip": dict(base=synth.PAPER, L=6000, N=300, k=300),
     # fp32 (the LDS-resident fp32 encoder)
     "tiny_f32": dict(base=synth.TINY, L=900, N=12),
 }

@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import synth
-from helpers import assert_select_equal, oracle_select, upload
+from helpers import assert_select_equal, launched_sites, oracle_select, upload
 from paper_2506_02267_amd import tav2 as T
 
 pytestmark = pytest.mark.gpu
@@ -78,11 +78,18 @@ def test_request_without_candidates():
     assert_select_equal(idx, score, ref_i, ref_s)
 
 
-@pytest.mark.parametrize("L", [100, 3000, 6000, 16384, 20000, 32768])
-def test_each_register_tile_size(L):
-    inp = custom_inputs([L], [9], d=32, levels=2, seed=L)
+@pytest.mark.parametrize("d", [48, 32])
+@pytest.mark.parametrize("L", [100, 1500, 3000, 6000, 16384, 20000, 32768])
+def test_each_register_tile_size(L, d):
+    """The top-k over score rows in memory (up to 4096 rows) and the search with scores on
+    chip; up to 8192 rows of d 32, the search in one launch."""
+    inp = custom_inputs([L], [9], d=d, levels=2, seed=L)
     k = min(1024, L)
     idx, score = run_select(inp, k)
+    seq, _, cands = upload(inp)
+    sites = launched_sites(lambda: T.nn_select(seq, cands, k))
+    assert ("nn_resident" in sites) == (d == 32 and L <= 8192)
+    assert ("topk" in sites) == (L <= 4096 and d == 48) and ("nn_select" in sites) == (L > 4096 and "nn_resident" not in sites)
     ref_i, ref_s = oracle.nn_select_batch(inp.seq, inp.cand, inp.cand_offset, k)
     assert_select_equal(idx, score, ref_i, ref_s)
 
@@ -324,6 +331,31 @@ def test_resident_equals_the_general_search(dtype, d, L):
         assert torch.all(s1[:7][hit] == 0)
         if k >= L:
             assert torch.all(hit.any(1))
+
+
+@pytest.mark.parametrize("n", [1, 31, 33])
+@pytest.mark.parametrize("d", [16, 240, 256, 272, 400, 512])
+def test_direct_scores_of_wide_rows(d, n):
+    """Few score tiles: products straight from memory, 16 k-blocks in flight (all of them up
+    to d 256; past it, partly and wholly refilled).  Against the oracle, and the same
+    candidates among enough others for the staged kernel: the same bits."""
+    print(f"direct scores d={d} n={n}", flush=True)
+    lengths = [300, 65, 0, 1]
+    assert sum(-(-max(lengths) // 256) * -(-c // 128) for c in [n] * 4) * d < 8192
+    inp = custom_inputs(lengths, [n] * 4, d=d, seed=d + n)
+    ref_i, ref_s = oracle.nn_select_batch(inp.seq, inp.cand, inp.cand_offset, 50)
+    idx, score = run_select(inp, 50)
+    assert_select_equal(idx, score, ref_i, ref_s)
+    # request 0 (2 tiles of 256 rows) alone, its candidates repeated past 8192 / d tiles
+    rep = -(-(128 * (4096 // d + 2)) // n)
+    one = synth.Inputs(w=inp.w, seq=synth.SeqBatch(emb=inp.seq.emb[:300], act=inp.seq.act[:300],
+                       time=inp.seq.time[:300], offset=np.zeros(1, np.int64),
+                       length=inp.seq.length[:1].copy()), cand=np.tile(inp.cand[:n], (rep, 1)),
+                       cand_offset=np.array([0, n * rep], np.int64))
+    i2, s2 = run_select(one, 50)
+    for at in (0, n * (rep // 2), n * (rep - 1)):
+        assert torch.equal(i2[at:at + n], idx[:n])
+        assert torch.equal(s2[at:at + n].view(torch.int32), score[:n].view(torch.int32))
 
 
 def ranged_inputs(dist, L, N, d, dtype, seed):

@@ -34,7 +34,9 @@ def both(inp, k):
 def test_two_calls_in_a_row_second_smaller(dtype):
     base = synth.SINGLE if dtype == "bf16" else synth.SELECT_I8
     big = synth.scaled(base, R=2, L=16384, N=300, k=256)
-    small = synth.scaled(base, R=1, L=9000, N=40, k=64)
+    # (both on the on-chip-score search, which uses the scratch: int8 rows of d 32 and at
+    # most 256 candidates would take the search in one launch)
+    small = synth.scaled(base, R=1, L=9000, N=40 if dtype == "bf16" else 260, k=64)
     print(f"no-alloc {dtype}: {big.R}x{big.N} at L={big.L}, then {small.R}x{small.N} at "
           f"L={small.L}", flush=True)
     inp1 = synth.make_inputs(big, seed=61)
