@@ -1015,7 +1015,7 @@ int device_cus() {
   return 256;
 }
 // Candidates side by side in a workgroup: as many as it takes to give every CU one
-// workgroup, at most what the LDS and 16 waves hold.
+// workgroup, at most what the LDS and GROUP_NW waves hold.
 int small_groups(int64_t total, const SmallPlan& p, const sm::Args& a, int cus) {
   if (p.blocks > 1) return 1;
   const int most = std::max(1, std::min(sm::GROUP_NW / p.nwc, small_pairs(a) / p.npair));

@@ -35,11 +35,15 @@ namespace tav2 {
 constexpr int SC_CANDS = 128;
 constexpr int SC_ROWS = 256;
 constexpr int SC_PAD = 8;   // LDS row padding (bf16) of the candidate tile
-// Tiles x d below this: the direct kernel (d 32: 17.6 us a search against 21.5 at 64
-// tiles, 22.8 against 24.2 at 128; d 256: 18.3 against 21.4 at 12 tiles; above it, re-reading
-// the operands costs more than it saves: 45.8 against 41.3 at 128 tiles of d 256,
-// 50.5 against 34.7 at 512 of d 64).
-constexpr int64_t SC_DIRECT = 8192;
+// At most so many tiles, and tiles x d below this: the direct kernel.  Above, re-reading the
+// operands costs more than the staging that it saves.  us a search, staged : direct:
+//   d     12 tiles     64           128          192          256          512
+//   16                                                        31.7 : 35.1  38.2 : 49.5 (496)
+//   48                 19.0 : 15.1  24.5 : 22.7  27.0 : 28.3  31.7 : 34.5
+//   64                 19.9 : 16.1  25.2 : 24.4                            41.4 : 59.3
+//   256   19.1 : 16.5  22.2 : 18.7 (32 tiles)    30.3 : 34.8 (128)
+//   512   26.0 : 21.4  28.3 : 23.0 (16)
+constexpr int64_t SC_DIRECT = 8192, SC_DIRECT_TILES = 128;
 
 __global__ __launch_bounds__(256) void score_bf16_kernel(
     const bf16_t* __restrict__ emb, const int64_t* __restrict__ seq_off,
@@ -301,8 +305,10 @@ __global__ __launch_bounds__(256) void score_f32_kernel(
 // NT: threads of a workgroup, PT: keys per thread (4 consecutive rows at a time).
 
 // At most this many candidates (two per CU): 512 threads each, half as many keys per
-// thread (100 candidates of 2000 rows, k 256: 13.5 us a search against 17.3; more
-// candidates hide the latency themselves: 2800 of 4000 rows 33.8 against 39.7).
+// thread; more candidates hide the latency themselves.  us a search, 256 : 512 threads:
+//   candidates   100          256          512          700          1000         2800
+//   2000 rows    11.4 : 11.1  11.9 : 11.6  13.3 : 13.0  14.4 : 14.3  15.9 : 16.2  30.3 : 33.0
+//   4000 rows    13.9 : 12.3  14.8 : 13.3  16.8 : 16.0  21.4 : 21.8  24.5 : 25.4  37.8 : 42.5
 constexpr int TK_WIDE = 512;
 
 // Exclusive prefix (in thread order) and block total of NV 64-bit values per
@@ -781,7 +787,8 @@ hipError_t launch_scores(const tav2_seq& seq, const tav2_cands& c, float* scores
     dim3 grid(unsigned(cdiv(seq.max_len, SC_ROWS)), unsigned(cdiv(c.max_count, SC_CANDS)),
               unsigned(seq.num_requests));
     ProfScope prof("score_bf16", st);
-    if (int64_t(grid.x) * grid.y * grid.z * seq.d < SC_DIRECT) {
+    const int64_t tiles = int64_t(grid.x) * grid.y * grid.z;
+    if (tiles <= SC_DIRECT_TILES && tiles * seq.d < SC_DIRECT) {
       grid.y = unsigned(cdiv(c.max_count, SD_CANDS));
       score_bf16_direct_kernel<<<grid, 256, 0, st>>>(
           static_cast<const bf16_t*>(seq.emb), seq.offset, seq.len,

@@ -16,8 +16,8 @@
 // one score, 256 candidates: 9.9 and 8.2 us; 27 and 30 with all 32 bits searched and the
 // selected rows counted; 16.5 by the launches that this kernel takes the place of).
 //
-// What bounds it: launch, first loads and selection are about 10 us; each 1024 rows add
-// 0.5 to 1 us: every workgroup reads all rows from L2 and turns codes into bf16.
+// What bounds it: launch, first loads and selection are 6 to 8 us; each 1024 rows add
+// about 1 us: every workgroup reads all rows from L2 and turns codes into bf16.
 #include <type_traits>
 
 #include "common.h"
@@ -33,7 +33,7 @@ struct Args {
   const int32_t* seq_len;
   const bf16_t* cand;
   const int64_t* cand_off;
-  int d, max_len, k, out_ld;
+  int max_len, k, out_ld;
   int32_t* out_idx;
   float* out_score;
   int32_t* cand_req;
@@ -310,22 +310,29 @@ __global__ __launch_bounds__(NT) void select_resident_kernel(Args A) {
 
 }  // namespace sr
 
-// One workgroup per CU, or two where the registers of two fit (up to 4 rows a thread).
+// One workgroup per CU, or two where the registers of two fit (up to 64: int8 of d 32 at two
+// rows a thread, bf16 at four).
 // us, this kernel : the launches it takes the place of; k 128, k 1000 at 8192 rows:
-//   candidates, d   rows 2000     4000        8192        16384
-//   256, 32 int8    11.4 : 15.3   11.6 : 20.3 15.5 : 44.0 25.1 : 29.0
-//   256, 32 bf16    11.1 : 13.6   11.1 : 18.6 15.5 : 50.2 (24.0 : 24.8)
-//   256, 64 int8    14.2 : 14.7   14.5 : 17.5 22.4 : 44.2 (39.8 : 30.1)
-//   500, 32 int8    13.4 : 16.6   17.9 : 21.8 (28.9 : 46.8) (47.5 : 33.7)
-//   500, 32 bf16    13.1 : 15.4   14.7 : 20.8
-//   256, 64 bf16    (13.2 : 14.7  21.3 : 17.5 42.8 : 52.1 71.2 : 27.2)
-// Those in brackets are not taken: rows above 64 bytes, more than 512 KB a request.
+//   candidates, d   rows 200     2000          4000          8192          16384
+//   8,   32 int8    7.1 : 8.9    7.0 : 10.2    9.1 : 11.8    13.6 : 29.7   19.6 : 24.5
+//   16,  32 int8    7.1 : 8.9    7.0 : 10.0    9.1 : 11.8    13.6 : 33.1   19.9 : 25.0
+//   256, 32 int8    7.3 : 9.3    7.4 : 11.0    9.7 : 13.1    15.2 : 42.3   22.3 : 28.0
+//   8,   32 bf16    6.4 : 7.6    7.1 : 8.9     9.3 : 10.3    14.2 : 33.2
+//   256, 32 bf16    6.7 : 8.3    7.5 : 9.9     10.0 : 12.1   15.3 : 49.3
+//   8,   64 int8    8.2 : 9.1    8.4 : 10.6    11.7 : 12.2   18.4 : 30.6
+//   256, 64 int8    8.8 : 9.7    8.9 : 11.3    12.9 : 13.5   21.1 : 44.2
+//   500, 32 int8                 10.7 : 12.7   (17.4 : 15.7)
+//   500, 32 bf16                 (13.0 : 11.7) (14.7 : 14.8)
+// Those in brackets are not taken; nor are rows above 64 bytes (256 of d 64 bf16: 21.3 us
+// at 4000 rows against 17.5 then) and more than 512 KB a request (256 of d 64 int8 at 16384
+// rows: 39.8 against 30.1).
 bool select_resident_applies(const tav2_seq& s, const tav2_cands& c) {
   if (s.dtype != TAV2_BF16 && s.dtype != TAV2_I8) return false;
   if (s.d != 32 && s.d != 64) return false;
   const int row = s.dtype == TAV2_I8 ? s.d : 2 * s.d;   // bytes
   if (row > 64 || int64_t(s.max_len) * row > 512 * 1024) return false;
-  return c.total <= 256 || (c.total <= 512 && s.d == 32 && s.max_len <= 4 * sr::NT);
+  return c.total <= 256 ||
+         (c.total <= 512 && s.dtype == TAV2_I8 && s.d == 32 && s.max_len <= 2 * sr::NT);
 }
 
 hipError_t launch_select_resident(const tav2_seq& seq, const tav2_cands& c, int k, int32_t* out_idx,
@@ -337,7 +344,6 @@ hipError_t launch_select_resident(const tav2_seq& seq, const tav2_cands& c, int 
   A.seq_len = seq.len;
   A.cand = static_cast<const bf16_t*>(c.emb);
   A.cand_off = c.offset;
-  A.d = seq.d;
   A.max_len = seq.max_len;
   A.k = k;
   A.out_ld = out_ld;
