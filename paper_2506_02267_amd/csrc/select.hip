@@ -432,8 +432,9 @@ __global__ __launch_bounds__(NT) void topk_kernel(
     if (tot >= kk) thr = probe;
   }
 
-  // Keys above thr go to sel[0, count_gt) in any order.  The need_eq lowest rows whose key
-  // equals thr follow them in row order, at their final places.  Rows are ordered by
+  // Keys above thr go to sel[0, count_gt) in any order (counting places them).  The need_eq
+  // lowest rows whose key equals thr follow them in row order, which is their place already.
+  // Rows are ordered by
   // (chunk, thread, u), so the equal keys are counted per chunk: 16-bit fields,
   // four chunks per 64-bit word, summed in one block scan with the above count.
   constexpr int NW = (NC + 3) / 4;
@@ -451,7 +452,6 @@ __global__ __launch_bounds__(NT) void topk_kernel(
   block_excl_scan<NW + 1, NT>(word, excl, total, scan_w, lane, wid);
   const int count_gt = int(total[0]);
   const int need_eq = kk - count_gt;
-  const float thr_score = key_score(thr);
   int gpos = int(excl[0]);
   int eq_before = 0;   // equal keys in chunks before c, over all threads
 #pragma unroll
@@ -466,15 +466,17 @@ __global__ __launch_bounds__(NT) void topk_kernel(
       if (kv > thr) {
         sel[gpos++] = sel_value(kv, row);
       } else if (kv == thr) {
-        if (e < need_eq) {
-          oi[count_gt + e] = row;
-          os[count_gt + e] = thr_score;
-        }
+        if (e < need_eq) sel[count_gt + e] = sel_value(kv, row);
         ++e;
       }
     }
   }
   __syncthreads();
+  // (stored from above, the addresses would take the kernel past 64 registers)
+  for (int p = count_gt + tid; p < kk; p += NT) {
+    oi[p] = sel_row(sel[p]);
+    os[p] = key_score(thr);
+  }
   place_by_rank<NT>(sel, count_gt, oi, os);
 }
 

@@ -320,26 +320,40 @@ __device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, ui
   kmin = max(kmin, 1u);
   kmax = max(kmax, kmin);
   KeyBins bin(kmin, kmax);
-  uint32_t last;
-  int total, cnt, was = 2 * NT * PER;
-  while (true) {
+  if (bin.shift == 0) {   // few different keys
 #pragma unroll
     for (int e = 0; e < PER; ++e)
       if (key(e) >= kmin) count_in_bin(hist, bin(key(e)));
-    __syncthreads();
-    last = find_bin<NT>(hist, red, uint32_t(kk), total, cnt);
-    tlo = 0u;
-    thi = ~0u;
-    if (last == ~0u) return false;
-    tlo = bin.bottom(last, kmin);
-    thi = bin.top(last);
-    const KeyBins finer(tlo, kmax);
-    if (!NARROW || cnt <= BIN_FEW || finer.shift >= bin.shift || (cnt <= BIN_MOST && 2 * cnt > was)) break;
-    was = cnt;
-    kmin = tlo;
-    bin = finer;
-    for (int b = threadIdx.x; b < NBINS; b += NT) hist[b] = 0u;
-    __syncthreads();
+  } else {
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (key(e) >= kmin) atomicAdd(&hist[bin(key(e))], 1u);
+  }
+  __syncthreads();
+  tlo = 0u;
+  thi = ~0u;
+  int total, cnt, was = 2 * NT * PER;
+  uint32_t last = find_bin<NT>(hist, red, uint32_t(kk), total, cnt);
+  if (last == ~0u) return false;
+  tlo = bin.bottom(last, kmin);
+  thi = bin.top(last);
+  if constexpr (NARROW) {
+    while (cnt > BIN_FEW && (cnt > BIN_MOST || 2 * cnt <= was)) {
+      const KeyBins finer(tlo, kmax);
+      if (finer.shift >= bin.shift) break;
+      kmin = tlo;
+      bin = finer;
+      was = cnt;
+      for (int b = threadIdx.x; b < NBINS; b += NT) hist[b] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        if (key(e) >= kmin) count_in_bin(hist, bin(key(e)));
+      __syncthreads();
+      last = find_bin<NT>(hist, red, uint32_t(kk), total, cnt);
+      tlo = bin.bottom(last, kmin);
+      thi = bin.top(last);
+    }
   }
   if (cnt > BIN_MOST) return false;
 #pragma unroll
