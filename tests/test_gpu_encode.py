@@ -7,7 +7,8 @@ import torch
 
 import oracle
 import synth
-from helpers import (BF16_TOL, F32_TOL, assert_select_equal, max_abs, oracle_select_encode,
+from helpers import (BF16_TOL, F32_TOL, assert_select_equal, max_abs,
+                     oracle_encode_tokens, oracle_select_encode,
                      strided_ids, upload, upload_tokens)
 from paper_2506_02267_amd import tav2 as T
 
@@ -292,3 +293,28 @@ def test_fp32_tables_aligned_to_floats_only(off):
         kept.append(buf)
         setattr(dw.s, name, buf.data_ptr() + 4 * off)
     assert torch.equal(T.encode(tok, cand, dw), ref)
+
+
+@pytest.mark.parametrize("n_heads,flags", [(8, T.MASK_CAUSAL), (4, T.MASK_NONE), (2, T.MASK_CAUSAL)])
+def test_fp32_infinite_keys_stay_with_their_head(n_heads, flags):
+    """Half of one head's keys overflow to infinity, with scores of -inf and weight 0; heads
+    that share a 16-feature tile with it (widths 4, 8 and 16) see nothing of them."""
+    print(f"fp32 infinite keys, {n_heads} heads, flags {flags}", flush=True)
+    dm = 32
+    W = synth.make_weights(synth.scaled(synth.TINY, d=32, d_model=dm, n_heads=n_heads, d_ffn=32,
+                                        n_layers=1, k=33, has_time=False))
+    L = W.layers[0]
+    W.W_in[:] = np.concatenate([np.eye(dm), np.zeros((dm, 32))], axis=1)
+    for a in (W.b_in, W.E_act, W.E_pos):
+        a[:] = 0
+    row = dm // n_heads + 1                        # a feature of the second head
+    L.W_qkv[row], L.b_qkv[row] = 0, -1
+    L.W_qkv[dm + row], L.b_qkv[dm + row] = 0, 0
+    L.W_qkv[dm + row, 1] = 3e38                    # key: 6e38 where x[1] is 2
+    tb = synth.make_tokens(4, 33, 32, has_time=False, seed=8, valid_len=[33, 17, 16, 2])
+    tb.emb[:, :, 1] = np.where(np.arange(33) % 2, 2, 0)
+    tok, cand = upload_tokens(tb, T.F32)
+    out = T.encode(tok, cand, T.DeviceWeights(W), flags=flags)
+    err = max_abs(out, oracle_encode_tokens(tb, W, causal=flags == T.MASK_CAUSAL))
+    print(f"  max abs error {err:.3e}", flush=True)
+    assert err <= F32_TOL
