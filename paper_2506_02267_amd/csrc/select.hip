@@ -345,8 +345,10 @@ __device__ __forceinline__ void block_excl_scan(const uint64_t (&v)[NV], uint64_
   }
 }
 
+// (8 waves a SIMD: 16 keys a thread would take 66 registers, and 2800 candidates of 4000 rows
+// 45.3 us for 44.5)
 template <int NT, int PT>
-__global__ __launch_bounds__(NT) void topk_kernel(
+__global__ __launch_bounds__(NT, 8) void topk_kernel(
     const float* __restrict__ scores, int64_t ld, const int64_t* __restrict__ cand_off,
     const int32_t* __restrict__ seq_len, int max_len, int k, int32_t* __restrict__ out_idx,
     float* __restrict__ out_score, int out_ld, int32_t* __restrict__ cand_req) {

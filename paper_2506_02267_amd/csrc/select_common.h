@@ -227,10 +227,17 @@ __device__ __forceinline__ void place_by_rank(const uint64_t* sel, int kk, int32
 // Bins as wide as the whole range are too coarse where it is wide (scores of both signs:
 // four bins to a factor of two), so the range is narrowed to what lies at or above the
 // kk-th value's bin, and binned again, while that makes the bins finer and that bin holds
-// more than a few values, or fewer than half of what it held (it does not shrink where it
+// more than a few values, and at most half of what it held (it does not shrink where it
 // holds equal scores).  Scores of both signs, rows of 16: 1000 candidates of 4000 rows at
 // kk = 256 and 700 at kk = 1000 take 22 and 23 us a search, and 56 and 103 with the first
-// pass's bins (37 and 81 by the bitwise search and counting).  NARROW off: one pass, for
+// pass's bins (37 and 81 by the bitwise search and counting).
+//
+// Where the kk-th value's bin still holds many values (equal scores: each would be compared
+// with all of them), that bin alone is binned again until the kk-th key is known, and the
+// caller places the keys above it by counting and the equal ones in row order.  Half of the
+// rows of one score: 8 requests of 100 to 1000 rows, 1600 candidates at kk = 100, 48 -> 20 us
+// (34 by the bitwise search); 1000 of 4096 rows at kk = 512, 56 -> 48 (52).  All of one score,
+// 3000 of 300 rows at kk = 8: 52 -> 15 (44).  NARROW off: one pass, for
 // keys that are known to lie above a close bound (the loop costs 22 registers there).
 //
 // key(e), row(e): the thread's elements e = 0 .. PER - 1 (key(e) = 0: none).  kmin,
@@ -238,12 +245,14 @@ __device__ __forceinline__ void place_by_rank(const uint64_t* sel, int kk, int32
 // out (at least kk are not).  hist (1024 words, zeroed, 16-byte aligned) and red (NT / 64
 // + 3 words) are LDS scratch; sorted holds at least kk + BIN_MOST - 1 values.  The caller
 // synchronises before (hist is zero).
-// Returns false, with nothing written, when there is no kk-th value or its bin holds
-// more than BIN_MOST values (many equal scores): the caller then selects another way, and
-// knows that the kk-th key lies in [tlo, thi].
+// Returns false, with nothing written, when there is no kk-th value or its bin holds too
+// many (more than BIN_MOST; with NARROW BIN_CLOSE: 64 and 256 take as long, 512 what the
+// figures above say): the caller then selects another way, and knows that the kk-th key lies
+// in [tlo, thi] (one key with NARROW, if there is one).
 constexpr int NBINS = 1024;
 constexpr int BIN_MOST = 512;
 constexpr int BIN_FEW = 32;
+constexpr int BIN_CLOSE = 128;
 // Bins of one width over the keys kmin .. kmax, the largest keys first.
 struct KeyBins {
   uint32_t kmax;
@@ -261,17 +270,20 @@ struct KeyBins {
     return past > uint64_t(kmax - kmin) ? kmin : kmax - uint32_t(past) + 1u;
   }
 };
-// One more value in bin b of hist.  Lanes that all count into one bin (equal scores) do so
-// at once: an LDS atomic takes its lanes' additions to one word one after the other.
+// One more value in bin b of hist.  The lanes that count into the first lane's bin (equal
+// scores) do so at once: an LDS atomic takes its lanes' additions to one word one after the
+// other.
 __device__ __forceinline__ void count_in_bin(uint32_t* hist, uint32_t b) {
   const uint32_t b0 = uint32_t(__builtin_amdgcn_readfirstlane(int(b)));
-  const uint64_t in = __builtin_amdgcn_ballot_w64(true);
-  if (__builtin_amdgcn_ballot_w64(b == b0) == in) {
-    if (__builtin_amdgcn_mbcnt_hi(uint32_t(in >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(in), 0)) == 0)
-      atomicAdd(&hist[b0], uint32_t(__popcll(in)));
-  } else {
-    atomicAdd(&hist[b], 1u);
-  }
+  const uint64_t same = __builtin_amdgcn_ballot_w64(b == b0);
+  const bool first = __builtin_amdgcn_mbcnt_hi(uint32_t(same >> 32),
+                                               __builtin_amdgcn_mbcnt_lo(uint32_t(same), 0)) == 0;
+  if (b != b0 || first) atomicAdd(&hist[b], b != b0 ? 1u : uint32_t(__popcll(same)));
+}
+// Whether many lanes of the wave hold the key of the lane before them.
+__device__ __forceinline__ bool keys_repeat(uint32_t k) {
+  const uint32_t prev = uint32_t(__builtin_amdgcn_update_dpp(0, int(k), 0x111, 0xf, 0xf, false));
+  return __popcll(__builtin_amdgcn_ballot_w64(k == prev && k != 0u)) >= 8;
 }
 // hist (complete: the caller has synchronised) becomes its exclusive prefix; returns
 // the bin that holds the need-th value (need >= 1) with `end` the values up to that
@@ -320,7 +332,9 @@ __device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, ui
   kmin = max(kmin, 1u);
   kmax = max(kmax, kmin);
   KeyBins bin(kmin, kmax);
-  if (bin.shift == 0) {   // few different keys
+  // few different keys, or many equal ones (wave-uniform; looked for only where a thread has
+  // many keys: with four, the look costs what the counting takes longer)
+  if (bin.shift == 0 || (NARROW && PER >= 8 && keys_repeat(key(0)))) {
 #pragma unroll
     for (int e = 0; e < PER; ++e)
       if (key(e) >= kmin) count_in_bin(hist, bin(key(e)));
@@ -338,7 +352,7 @@ __device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, ui
   tlo = bin.bottom(last, kmin);
   thi = bin.top(last);
   if constexpr (NARROW) {
-    while (cnt > BIN_FEW && (cnt > BIN_MOST || 2 * cnt <= was)) {
+    while (cnt > BIN_FEW && 2 * cnt <= was) {
       const KeyBins finer(tlo, kmax);
       if (finer.shift >= bin.shift) break;
       kmin = tlo;
@@ -355,7 +369,28 @@ __device__ __forceinline__ bool place_by_bins(const Key& key, const Row& row, ui
       thi = bin.top(last);
     }
   }
-  if (cnt > BIN_MOST) return false;
+  if constexpr (NARROW) {
+    if (cnt > BIN_CLOSE) {   // the kk-th key by bins of its bin
+      uint32_t need = uint32_t(kk - (total - cnt));
+      while (tlo != thi) {
+        const KeyBins within(tlo, thi);
+        for (int b = threadIdx.x; b < NBINS; b += NT) hist[b] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < PER; ++e)
+          if (key(e) >= tlo && key(e) <= thi) count_in_bin(hist, within(key(e)));
+        __syncthreads();
+        int end, n;
+        const uint32_t b = find_bin<NT>(hist, red, need, end, n);
+        need -= uint32_t(end - n);
+        tlo = within.bottom(b, tlo);
+        thi = within.top(b);
+      }
+      return false;
+    }
+  } else {
+    if (cnt > BIN_MOST) return false;
+  }
 #pragma unroll
   for (int e = 0; e < PER; ++e)
     if (key(e) >= kmin) {

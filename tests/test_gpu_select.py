@@ -404,3 +404,26 @@ def test_score_ranges(dist, dtype, d, L, N):
         idx, score = run_select(inp, k)
         ref_i, ref_s = oracle_select(inp, k, ids=ids)
         assert_select_equal(idx, score, ref_i, ref_s, ids=ids)
+
+
+@pytest.mark.parametrize("dtype,d,L,N", [
+    ("bf16", 16, 700, 4), ("bf16", 16, 2000, 600), ("bf16", 16, 4000, 3),   # score rows in memory
+    ("f32", 16, 1100, 3), ("bf16", 32, 1500, 4)])                           # (the last: one launch)
+@pytest.mark.parametrize("group", [31, 33, 127, 129, 255, 513, 650])
+def test_equal_scores_at_the_last_place(group, dtype, d, L, N):
+    """A group of rows of one score around the k-th place, of sizes about those at which
+    placement by bins hands over (32, 128, 512), with k at its ends, inside it and where the
+    group is about half of k; the scores around it are all different."""
+    print(f"equal group {group} {dtype} d={d} L={L} N={N}", flush=True)
+    inp = ranged_inputs("both_signs", L, N, d, dtype, seed=group)
+    rng = np.random.default_rng(group)
+    e = inp.seq.emb
+    e[rng.choice(L, group, replace=False), :2] = (1.0, 2.0 ** -13)
+    above = int((e[:, :2].sum(1) > 1.0 + 2.0 ** -13).sum())
+    ids = np.arange(N) if N <= 8 else np.unique(np.r_[0:8, N - 1])
+    for k in sorted({above, above + 1, above + group // 2, above + group, above + group + 1, 2 * group}):
+        if not 1 <= k <= min(L, 1024):
+            continue
+        idx, score = run_select(inp, k)
+        ref_i, ref_s = oracle_select(inp, k, ids=ids)
+        assert_select_equal(idx, score, ref_i, ref_s, ids=ids)
