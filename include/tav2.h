@@ -230,14 +230,17 @@ tav2_status tav2_gather(const tav2_seq* seq, const tav2_seq* rt, const tav2_cand
                         int32_t* valid_len, void* stream);
 
 /*
- * Packed encoder weights: the bf16 encoder reads its matrices and side tables in
- * its own fragment order (dm 64: the layer weights, W_in's token half and W_pool
- * as operand fragments, which the kernel copies into LDS as they stand).  tav2_pack_weights writes that form once into a
+ * Packed encoder weights: the bf16 encoders read most of their weights in their own
+ * fragment order (dm 256: the layer matrices with their biases, W_in's token half,
+ * W_pool and the side tables; dm 64: the layer matrices and vectors and W_in's token
+ * half).  tav2_pack_weights writes that form once into a
  * caller-owned device buffer of tav2_pack_weights_bytes(w) bytes (256-byte
  * aligned); a tav2_weights whose `packed` points at it skips the packing step
  * of every later call (the paper's serving engine likewise keeps its model in
  * pre-allocated device memory, Sec. 3.4.2).  The buffer stays valid while the
- * weights it was packed from are unchanged; it is read-only to the library.
+ * weights it was packed from are unchanged; it is read-only to the library.  What it
+ * does not hold is read from the weights' own arrays in every call, which therefore
+ * stay allocated and unchanged as well.
  * float32 weights are used as given: 0 bytes, and packing them is a no-op.
  * Errors: TAV2_ERR_NULL, TAV2_ERR_SHAPE, TAV2_ERR_DTYPE, TAV2_ERR_UNSUPPORTED,
  * TAV2_ERR_WORKSPACE (buffer NULL, misaligned or too small), TAV2_ERR_HIP.
@@ -335,7 +338,8 @@ tav2_status tav2_select_encode_eq2(const tav2_seq* seq, const tav2_eq2* eq2,
  * to buf_bytes), forgets the recorded launches and returns the untruncated
  * text length.  Site names: seq_view, nn_sample, nn_threshold, nn_filter, nn_select,
  * nn_fallback (the NN search with on-chip scores, for bf16 and int8 sequences of
- * more than 4096 rows), score_bf16, score_i8, score_f32, topk (the NN search over
+ * more than 4096 rows), nn_resident (the search in one launch: rows of at most 64 bytes
+ * with d 32 or 64, few candidates), score_bf16, score_i8, score_f32, topk (the NN search over
  * materialised score rows), gather, pack_weights, cand_proj, encoder_fused (the
  * bf16 encoder of d_model 256), encoder_small (d_model 64), encode_f32.
  */

@@ -18,9 +18,9 @@
 // What bounds it: a candidate's chain of products on one SIMD per 16 tokens (32 cycles a
 // step) and the latency of the weight stream, which is kept PF row tiles ahead, across
 // the products' ends.  16 candidates of 32 positions (d_model 64, FFN 128, one layer):
-// a search and 23 us, where LDS-staged products on the vector units (a register tile
-// per thread, two LDS reads a k step, a weight chunk's barriers) took 74; 1600 of 60
-// positions, two layers, 350 us with the search (1379).
+// 27.5 us, where LDS-staged products on the vector units (a register tile per thread, two
+// LDS reads a k step, a weight chunk's barriers) took 73; 1600 of 60 positions, two layers,
+// 368 us (1545).
 #include "common.h"
 #include "internal.h"
 #include "token_source.h"
