@@ -38,8 +38,8 @@
 // positions: 21.4 us (37.8 us with 4 waves per candidate taking blocks of 64 positions
 // in turn and activations passed through LDS), of 64: 12.9 us (15.2), of 256: 36.2 us
 // (49.4); 200 of 300 to 1024: 175 us (318); 2000 of 192: 120 us (255); 2000 of 13 to 26:
-// 23.1 us (77.9): back-to-back calls on explicit tokens, by events.  More waves (16 of at most 128 registers) spill: 64 us at 192
-// positions.  More than 128 positions a block when there are several (192 against
+// 23.1 us (77.9): back-to-back calls on explicit tokens, by events.  More waves (16 of at
+// most 128 registers) spill: 64 us at 192 positions.  More than 128 positions a block when there are several (192 against
 // 128): 173 us against 197 at 1024 positions, 565 against 665 at 2048.
 #include <algorithm>
 #include <atomic>
